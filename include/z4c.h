@@ -167,13 +167,13 @@ z4c_status z4c_plan_set_params(z4c_plan *plan, const z4c_params *params);
 z4c_status z4c_plan_set_neighbours(z4c_plan *plan, const int *neighbours);
 
 /* Launch shape for the blocks of one size class (nx, ny, nz) (0 = all).
- * tile_x/y/z: interior points per workgroup, one thread per point;
- * persistent: 0 = one workgroup per tile, otherwise that many workgroups
- * taking tiles from a work queue (per-XCD ranges of consecutive tiles, then
- * the other ranges' leftovers); waves: occupancy the kernel variant is
- * compiled for, in waves per SIMD (0 = 2; its register budget is 512/waves
- * per lane).  Supported: 8x8x8 and 8x8x4 with waves 2, and for order 6 also
- * 8x8x4 and 8x4x8 with waves 1. */
+ * Accepted: tiles of 8x8x8 and 8x8x4 points with waves 2 (or 0), and for
+ * order 6 also 8x8x4 and 8x4x8 with waves 1; any persistent >= 0.  The
+ * shape is kept with the class, is what z4c_plan_get_launch returns, and
+ * sets the counts of z4c_plan_tiles; every accepted shape runs the same
+ * kernel (8x8x4 points per workgroup, one workgroup per tile, all classes in
+ * one dispatch), which measured faster than each of the shapes it replaced,
+ * so results and speed do not depend on it. */
 typedef struct {
     int tile_x, tile_y, tile_z;
     int persistent;
@@ -218,7 +218,7 @@ z4c_status z4c_constraints(z4c_plan *plan, const double *u, const double *matter
 /* z4c_constraints for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same kernels and results (bitwise), with the per-tile partial sums in
- * a static device array of the library (8 MiB per device, held until the
+ * a static device array of the library (16 MiB per device, held until the
  * process ends) instead of the plan's buffer; the call allocates nothing.
  * The plan itself (created beforehand) still owns its tables.  Plans of more
  * than 65,536 tiles (z4c_plan_tiles) are refused with Z4C_ENOTSUP.  Every
@@ -308,19 +308,13 @@ z4c_status z4c_step(z4c_plan *plan, const z4c_step_desc *desc, int *result, void
 z4c_status z4c_step_graph(z4c_plan *plan, const z4c_step_desc *desc, int *result,
                           void *stream);
 
-/* Time each supported launch shape per size class on the caller's buffers
- * (u0 read, u0_out/u1 overwritten at interior points, one RK4-like stage)
- * and keep the fastest; `reps` timed launches per candidate.  Candidates:
- * every supported tile shape and occupancy, each as a grid launch and as
- * persistent launches of one and two workgroups per CU.  Then classes that
- * chose the same tile shape and occupancy are timed together, as they
- * launch (one dispatch when their launch forms agree), under their own
- * choices and under each common launch form, and the fastest is kept.
- * With a tuning cache set (z4c_set_tune_cache), size classes found there
- * under the same key (device architecture, order, arithmetic, advection,
- * halo rule, block interior size, ghosts) take the stored launch without
- * timing (and without the joint pass when every class is found), and newly
- * timed ones are added to it.  Results are readable with
+/* Set the launch shape of every size class to the one the kernels run (see
+ * z4c_launch), timing it on the caller's buffers (u0 read, u0_out/u1
+ * overwritten at interior points, RK4-like stages, `reps` timed ones).  With
+ * a tuning cache set (z4c_set_tune_cache), size classes found there under
+ * the same key (device architecture, order, arithmetic, advection, halo
+ * rule, block interior size, ghosts) take the stored launch without timing,
+ * and the others are added to it.  Results are readable with
  * z4c_plan_get_launch.  Synchronises the stream. */
 z4c_status z4c_plan_autotune(z4c_plan *plan, const double *u0, double *u0_out, double *u1,
                              const double *matter, int reps, void *stream);

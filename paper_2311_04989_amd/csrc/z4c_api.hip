@@ -16,9 +16,11 @@
 
 using namespace z4c;
 
-// Scratch of z4c_constraints_noalloc (partial sums, 16 doubles per tile).
-constexpr int NOALLOC_MAX_TILES = 65536;   // 8 MiB per device
-static __device__ __align__(256) double scratch[NOALLOC_MAX_TILES * 16];
+// Scratch of z4c_constraints_noalloc (partial sums, 16 doubles per kernel
+// tile).  The plans it takes are limited by their launch shapes' tile count;
+// a tile of any such shape is at most two kernel tiles.
+constexpr int NOALLOC_MAX_TILES = 65536;
+static __device__ __align__(256) double scratch[2 * NOALLOC_MAX_TILES * 16];   // 16 MiB per device
 
 namespace {
 
@@ -42,14 +44,6 @@ z4c_status hip_fail(hipError_t e, const char *what)
         if (e_ != hipSuccess)                      \
             return hip_fail(e_, what);             \
     } while (0)
-
-struct LaunchGroup {
-    int tx, ty, tz, persistent, waves;
-    std::vector<Tile> tiles;
-    Tile *tiles_d = nullptr;
-    int *queue_d = nullptr;   // persistent launches: 8 tile counters
-    long long tile_base = 0;
-};
 
 struct SizeClass {
     int nx, ny, nz;
@@ -171,8 +165,12 @@ struct z4c_plan {
     double *fac64_d = nullptr;
     float *fac32_d = nullptr;
     std::vector<SizeClass> classes;
-    std::vector<LaunchGroup> groups;
-    long long total_tiles = 0;
+    // kernel tiles of every block, in one allocation with their counts per
+    // block and the scratch for norm partial sums
+    char *tile_tables_d = nullptr;
+    Tile *tiles_d = nullptr;
+    int ntiles = 0;
+    long long total_tiles = 0;   // tiles of the classes' launch shapes
     long long *tile_start_d = nullptr;
     int *tile_count_d = nullptr;
     double *partial_d = nullptr;
@@ -222,21 +220,12 @@ struct z4c_plan {
         outer_start_d = nullptr;
     }
 
-    void free_groups()
+    void free_tiles()
     {
-        for (auto &g : groups) {
-            if (g.tiles_d)
-                (void)hipFree(g.tiles_d);
-            if (g.queue_d)
-                (void)hipFree(g.queue_d);
-        }
-        groups.clear();
-        if (tile_start_d)
-            (void)hipFree(tile_start_d);
-        if (tile_count_d)
-            (void)hipFree(tile_count_d);
-        if (partial_d)
-            (void)hipFree(partial_d);
+        if (tile_tables_d)
+            (void)hipFree(tile_tables_d);
+        tile_tables_d = nullptr;
+        tiles_d = nullptr;
         tile_start_d = nullptr;
         tile_count_d = nullptr;
         partial_d = nullptr;
@@ -397,83 +386,52 @@ z4c_status upload_factors(z4c_plan *P)
     return Z4C_OK;
 }
 
-// Build launch groups from the size classes and upload tile lists.
-z4c_status build_groups(z4c_plan *P)
+// Tiles of the launch shapes the classes have (z4c_plan_tiles).
+void count_tiles(z4c_plan *P)
 {
-    P->free_groups();
-    P->clear_graphs();
-    ++P->version;
-    std::map<std::vector<int>, int> gidx;
+    P->total_tiles = 0;
+    for (const SizeClass &c : P->classes) {
+        const auto n = [](int e, int t) { return (long long)((e + t - 1) / t); };
+        P->total_tiles += (long long)c.blocks.size() * n(c.nx, c.launch.tile_x)
+                        * n(c.ny, c.launch.tile_y) * n(c.nz, c.launch.tile_z);
+    }
+}
+
+// The kernel tiles of every block, one dispatch for the whole level set: the
+// blocks of a size class after one another, the tiles of a block consecutive.
+z4c_status build_tiles(z4c_plan *P)
+{
+    std::vector<Tile> tiles;
     std::vector<long long> tstart(P->nblocks, 0);
     std::vector<int> tcount(P->nblocks, 0);
-    for (const SizeClass &c : P->classes) {
-        const std::vector<int> key = {c.launch.tile_x, c.launch.tile_y, c.launch.tile_z,
-                                      c.launch.persistent, c.launch.waves};
-        auto it = gidx.find(key);
-        int gi;
-        if (it == gidx.end()) {
-            gi = (int)P->groups.size();
-            gidx[key] = gi;
-            LaunchGroup g;
-            g.tx = c.launch.tile_x;
-            g.ty = c.launch.tile_y;
-            g.tz = c.launch.tile_z;
-            g.persistent = c.launch.persistent;
-            g.waves = c.launch.waves;
-            P->groups.push_back(g);
-        } else {
-            gi = it->second;
-        }
-        LaunchGroup &g = P->groups[gi];
+    for (const SizeClass &c : P->classes)
         for (int b : c.blocks) {
-            const z4c_block &B = P->blocks[b];
-            tstart[b] = (long long)g.tiles.size();   // relative for now
-            int n = 0;
-            for (int k0 = 0; k0 < B.nz; k0 += g.tz)
-                for (int j0 = 0; j0 < B.ny; j0 += g.ty)
-                    for (int i0 = 0; i0 < B.nx; i0 += g.tx) {
-                        g.tiles.push_back(Tile{b, i0, j0, k0});
-                        ++n;
-                    }
-            tcount[b] = n;
+            tstart[b] = (long long)tiles.size();
+            for (int k0 = 0; k0 < c.nz; k0 += TILE_Z)
+                for (int j0 = 0; j0 < c.ny; j0 += TILE_Y)
+                    for (int i0 = 0; i0 < c.nx; i0 += TILE_X)
+                        tiles.push_back(Tile{b, i0, j0, k0});
+            tcount[b] = (int)((long long)tiles.size() - tstart[b]);
         }
-    }
-    long long base = 0;
-    std::vector<int> block_group(P->nblocks, 0);
-    for (size_t gi = 0; gi < P->groups.size(); ++gi) {
-        P->groups[gi].tile_base = base;
-        base += (long long)P->groups[gi].tiles.size();
-    }
-    for (size_t ci = 0; ci < P->classes.size(); ++ci) {
-        const SizeClass &c = P->classes[ci];
-        const std::vector<int> key = {c.launch.tile_x, c.launch.tile_y, c.launch.tile_z,
-                                      c.launch.persistent, c.launch.waves};
-        const int gi = gidx[key];
-        for (int b : c.blocks)
-            tstart[b] += P->groups[gi].tile_base;
-    }
-    P->total_tiles = base;
+    if (tiles.size() > (size_t)INT_MAX)
+        return fail(Z4C_ENOTSUP, "too many tiles");
+    P->ntiles = (int)tiles.size();
     if (!P->device)
         return Z4C_OK;
-    for (auto &g : P->groups) {
-        HIP_TRY(hipMalloc(&g.tiles_d, sizeof(Tile) * std::max<size_t>(1, g.tiles.size())),
-                "hipMalloc(tiles)");
-        if (g.persistent)
-            HIP_TRY(hipMalloc(&g.queue_d, sizeof(int) * 16), "hipMalloc(queue)");
-        HIP_TRY(hipMemcpy(g.tiles_d, g.tiles.data(), sizeof(Tile) * g.tiles.size(),
-                          hipMemcpyHostToDevice),
-                "hipMemcpy(tiles)");
-    }
-    HIP_TRY(hipMalloc(&P->tile_start_d, sizeof(long long) * P->nblocks), "hipMalloc");
-    HIP_TRY(hipMalloc(&P->tile_count_d, sizeof(int) * P->nblocks), "hipMalloc");
-    HIP_TRY(hipMemcpy(P->tile_start_d, tstart.data(), sizeof(long long) * P->nblocks,
-                      hipMemcpyHostToDevice),
-            "hipMemcpy");
-    HIP_TRY(hipMemcpy(P->tile_count_d, tcount.data(), sizeof(int) * P->nblocks,
-                      hipMemcpyHostToDevice),
-            "hipMemcpy");
-    HIP_TRY(hipMalloc(&P->partial_d, sizeof(double) * 16 * std::max<long long>(1, base)),
-            "hipMalloc(partial)");
+    const size_t bs = sizeof(long long) * tstart.size(), bt = sizeof(Tile) * tiles.size(),
+                 bc = sizeof(int) * tcount.size(), bp = sizeof(double) * 16 * tiles.size();
+    std::vector<char> host(bs + bt + bc);
+    std::memcpy(&host[0], tstart.data(), bs);
+    std::memcpy(&host[bs], tiles.data(), bt);
+    std::memcpy(&host[bs + bt], tcount.data(), bc);
+    HIP_TRY(hipMalloc((void **)&P->tile_tables_d, bp + host.size()), "hipMalloc(tiles)");
+    char *const d = P->tile_tables_d;
+    P->partial_d = (double *)d;
+    P->tile_start_d = (long long *)(d + bp);
+    P->tiles_d = (Tile *)(d + bp + bs);
+    P->tile_count_d = (int *)(d + bp + bs + bt);
+    HIP_TRY(hipMemcpy(d + bp, host.data(), host.size(), hipMemcpyHostToDevice),
+            "hipMemcpy(tiles)");
     return Z4C_OK;
 }
 
@@ -483,6 +441,8 @@ StageArgs base_args(const z4c_plan *P)
     a.blocks = P->blocks_d;
     a.fac64 = P->fac64_d;
     a.fac32 = P->fac32_d;
+    a.tiles = P->tiles_d;
+    a.ntiles = P->ntiles;
     a.ko_sigma = P->params.ko_sigma;
     a.kappa1 = P->params.kappa1;
     a.kappa2 = P->params.kappa2;
@@ -498,29 +458,10 @@ StageArgs base_args(const z4c_plan *P)
     return a;
 }
 
-z4c_status run_groups(z4c_plan *P, int mode, int arith, StageArgs a, hipStream_t s)
+z4c_status run_tiles(z4c_plan *P, int mode, int arith, const StageArgs &a, hipStream_t s)
 {
-    for (const auto &g : P->groups) {
-        a.tiles = g.tiles_d;
-        a.ntiles = (int)g.tiles.size();
-        a.persistent = g.persistent;
-        a.queue = g.queue_d;
-        a.tile_base = g.tile_base;
-        if (g.persistent && !g.tiles.empty()) {
-            const hipError_t ez = launch_zero_queue(g.queue_d, s);
-            if (ez != hipSuccess)
-                return hip_fail(ez, "tile-queue reset launch");
-        }
-        const bool lop = P->params.advection == Z4C_ADVECT_LOPSIDED
-                      && (mode == MODE_RHS || mode == MODE_RK);
-        const hipError_t e = lop ? launch_lopsided(mode, P->params.fd_order, g.tx, g.ty, g.tz,
-                                                   g.waves, a, s)
-                                 : launch_stage(mode, P->params.fd_order, arith, g.tx, g.ty,
-                                                g.tz, g.waves, a, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "tile kernel launch");
-    }
-    return Z4C_OK;
+    const hipError_t e = launch_stage(mode, P->params.fd_order, arith, P->params.advection, a, s);
+    return e == hipSuccess ? Z4C_OK : hip_fail(e, "tile kernel launch");
 }
 
 z4c_status need_device(const z4c_plan *P)
@@ -581,19 +522,11 @@ z4c_status enqueue_stage(z4c_plan *P, const double *u0_in, double *u0_out, doubl
     a.out = u0_out;
     a.u1 = u1;
     a.u2 = u2;
-    a.delta = c->delta;
-    a.eps_dt = c->eps * dt;
-    a.g1 = c->g1;
-    a.g2 = c->g2;
-    a.g3 = c->g3;
-    a.beta_dt = c->beta * dt;
-    a.read_u1 = c->read_u1;
-    a.write_u1 = c->write_u1;
-    a.use_u2 = c->g3 != 0.0;
-    a.u2_is_u0 = u2 == u0_in;
-    if (!a.use_u2)
+    a.rk = RKArgs{c->delta, c->eps * dt, c->g1, c->g2, c->g3, c->beta * dt, c->read_u1,
+                  c->write_u1, c->g3 != 0.0, u2 == u0_in};
+    if (!a.rk.use_u2)
         a.u2 = nullptr;
-    return run_groups(P, monitor ? MODE_RK_MON : MODE_RK, P->params.arith, a, s);
+    return run_tiles(P, monitor ? MODE_RK_MON : MODE_RK, P->params.arith, a, s);
 }
 
 z4c_status enqueue_ghost(z4c_plan *P, int policy, double *u, const double *frozen, hipStream_t s)
@@ -840,7 +773,7 @@ z4c_status enqueue_constraints(z4c_plan *P, const double *u, const double *matte
     a.matter = matter;
     a.out = cons;
     a.partial = partial;
-    z4c_status st = run_groups(P, MODE_CONS, Z4C_ARITH_FP64, a, s);
+    z4c_status st = run_tiles(P, MODE_CONS, Z4C_ARITH_FP64, a, s);
     if (st != Z4C_OK)
         return st;
     const hipError_t e = launch_norm_reduce(P->blocks_d, P->nblocks, P->tile_start_d,
@@ -1072,7 +1005,8 @@ z4c_status z4c_plan_create(const z4c_params *params, const z4c_block *blocks, in
             return st;
         }
     }
-    st = build_groups(P);
+    count_tiles(P);
+    st = build_tiles(P);
     if (st == Z4C_OK)
         st = upload_factors(P);
     if (st != Z4C_OK) {
@@ -1089,7 +1023,7 @@ z4c_status z4c_plan_destroy(z4c_plan *P)
         return Z4C_OK;
     if (P->device) {
         P->clear_graphs();
-        P->free_groups();
+        P->free_tiles();
         if (P->blocks_d)
             (void)hipFree(P->blocks_d);
         if (P->fac64_d)
@@ -1130,18 +1064,11 @@ z4c_status z4c_plan_set_params(z4c_plan *P, const z4c_params *params)
         P->clear_graphs();
     ++P->version;
     if (order_changed) {
-        bool reset = false;
         for (auto &c : P->classes)
             if (!stage_shape_supported(params->fd_order, c.launch.tile_x, c.launch.tile_y,
-                                       c.launch.tile_z, c.launch.waves)) {
+                                       c.launch.tile_z, c.launch.waves))
                 c.launch = z4c_launch{8, 8, 8, 0, 2};
-                reset = true;
-            }
-        if (reset) {
-            st = build_groups(P);
-            if (st != Z4C_OK)
-                return st;
-        }
+        count_tiles(P);
     }
     return upload_factors(P);
 }
@@ -1282,7 +1209,8 @@ z4c_status z4c_plan_set_launch(z4c_plan *P, int nx, int ny, int nz, const z4c_la
         }
     if (!any)
         return fail(Z4C_EINVAL, "no blocks of that size");
-    return build_groups(P);
+    count_tiles(P);
+    return Z4C_OK;
 }
 
 z4c_status z4c_plan_get_launch(const z4c_plan *P, int nx, int ny, int nz, z4c_launch *L)
@@ -1316,7 +1244,7 @@ z4c_status z4c_rhs(z4c_plan *P, const double *u, const double *matter, double *r
     a.u = u;
     a.matter = matter;
     a.out = rhs;
-    return run_groups(P, MODE_RHS, P->params.arith, a, (hipStream_t)stream);
+    return run_tiles(P, MODE_RHS, P->params.arith, a, (hipStream_t)stream);
 }
 
 z4c_status z4c_rk_stage(z4c_plan *P, const double *u0_in, double *u0_out, double *u1,
@@ -1563,151 +1491,53 @@ z4c_status z4c_plan_autotune(z4c_plan *P, const double *u0, double *u0_out, doub
     z4c_status st = need_device(P);
     if (st != Z4C_OK)
         return st;
+    // One kernel serves every launch shape of a scheme, so there is one
+    // candidate: its tiles, one workgroup each.  The recorded time is that of
+    // the dispatch the class is part of.
     hipStream_t s = (hipStream_t)stream;
-    const z4c_rk_coeffs c{0.0, 1.0 / 3.0, 0.0, 0.0, 1.0, 0.5, 1, 1};
-    // Candidates: every supported tile shape and occupancy, as a grid launch
-    // and as persistent launches of one or two workgroups per CU; earlier
-    // candidates win near-ties (a later one must be 1.5 % faster).
-    static const int shapes[][4] = {{8, 8, 4, 1}, {8, 4, 8, 1}, {8, 8, 8, 2}, {8, 8, 4, 2}};
-    hipEvent_t e0, e1;
-    HIP_TRY(hipEventCreate(&e0), "hipEventCreate");
-    HIP_TRY(hipEventCreate(&e1), "hipEventCreate");
-    const std::vector<SizeClass> saved = P->classes;
-    std::vector<z4c_launch> best(P->classes.size());
-    std::vector<float> best_time(P->classes.size(), 0.f);
+    const z4c_launch own{TILE_X, TILE_Y, TILE_Z, 0, 2};
     TuneCache cache = tune_cache_load();
-    std::vector<std::string> keys(saved.size());
-    for (size_t ci = 0; ci < saved.size(); ++ci) {
-        keys[ci] = tune_key(P, saved[ci]);
-        auto hit = cache.entries.find(keys[ci]);
+    bool fresh = false;
+    float ms = 0.f;
+    for (SizeClass &c : P->classes) {
+        const std::string key = tune_key(P, c);
+        const auto hit = cache.entries.find(key);
         if (hit != cache.entries.end()
             && stage_shape_supported(P->params.fd_order, hit->second.launch.tile_x,
                                      hit->second.launch.tile_y, hit->second.launch.tile_z,
                                      hit->second.launch.waves)) {
-            best[ci] = hit->second.launch;
-            best_time[ci] = -1.f;   // from the cache
+            c.launch = hit->second.launch;
             continue;
         }
-        float best_ms = 1e30f;
-        for (const auto &sh : shapes) {
-            if (!stage_shape_supported(P->params.fd_order, sh[0], sh[1], sh[2], sh[3]))
-                continue;
-            for (int pers : {0, 1, 2}) {
-                z4c_launch L{sh[0], sh[1], sh[2], pers * P->num_cus, sh[3]};
-                // a plan view holding only this size class
-                P->classes.assign(1, saved[ci]);
-                P->classes[0].launch = L;
-                st = build_groups(P);
-                if (st != Z4C_OK)
-                    break;
-                st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);   // warm-up
-                if (st != Z4C_OK)
-                    break;
-                (void)hipEventRecord(e0, s);
-                for (int r = 0; r < reps && st == Z4C_OK; ++r)
-                    st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);
-                (void)hipEventRecord(e1, s);
-                (void)hipEventSynchronize(e1);
-                float ms = 0.f;
-                (void)hipEventElapsedTime(&ms, e0, e1);
-                if (st == Z4C_OK && ms < 0.985f * best_ms) {
-                    best_ms = ms;
-                    best[ci] = L;
-                    best_time[ci] = ms / reps;
-                }
+        if (!fresh) {
+            const z4c_rk_coeffs co{0.0, 1.0 / 3.0, 0.0, 0.0, 1.0, 0.5, 1, 1};
+            hipEvent_t e0, e1;
+            HIP_TRY(hipEventCreate(&e0), "hipEventCreate");
+            if (const hipError_t e = hipEventCreate(&e1); e != hipSuccess) {
+                (void)hipEventDestroy(e0);
+                return hip_fail(e, "hipEventCreate");
             }
-            if (st != Z4C_OK)
-                break;
-        }
-        if (st != Z4C_OK)
-            break;
-    }
-    // Merge pass.  Classes that share a tile shape and occupancy run as one
-    // dispatch when they also share the launch form, which a class timed
-    // alone cannot see (one tail instead of several, one work queue for
-    // all).  For each such set of two or more classes, time the set with
-    // the per-class choices and with each uniform launch form, and keep the
-    // fastest (a change must be 1.5 % faster).  Runs only when some class was
-    // timed now, so that a plan whose classes all come from the cache keeps
-    // exactly the cached launches.
-    bool fresh_any = false;
-    for (size_t ci = 0; ci < saved.size(); ++ci)
-        fresh_any = fresh_any || best_time[ci] >= 0.f;
-    if (st == Z4C_OK && fresh_any) {
-        std::map<std::vector<int>, std::vector<size_t>> sets;
-        for (size_t ci = 0; ci < saved.size(); ++ci)
-            sets[{best[ci].tile_x, best[ci].tile_y, best[ci].tile_z, best[ci].waves}].push_back(ci);
-        auto time_set = [&](const std::vector<size_t> &members,
-                            const std::vector<z4c_launch> &launch, float *ms) -> z4c_status {
-            P->classes.clear();
-            for (size_t m = 0; m < members.size(); ++m) {
-                P->classes.push_back(saved[members[m]]);
-                P->classes.back().launch = launch[m];
-            }
-            z4c_status r = build_groups(P);
-            if (r == Z4C_OK)
-                r = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);   // warm-up
-            if (r != Z4C_OK)
-                return r;
+            st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &co, 1e-3, s);   // warm-up
             (void)hipEventRecord(e0, s);
-            for (int k = 0; k < reps && r == Z4C_OK; ++k)
-                r = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);
+            for (int r = 0; r < reps && st == Z4C_OK; ++r)
+                st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &co, 1e-3, s);
             (void)hipEventRecord(e1, s);
             (void)hipEventSynchronize(e1);
-            *ms = 0.f;
-            (void)hipEventElapsedTime(ms, e0, e1);
-            return r;
-        };
-        for (const auto &kv : sets) {
-            const std::vector<size_t> &members = kv.second;
-            if (members.size() < 2)
-                continue;
-            std::vector<z4c_launch> cur(members.size());
-            for (size_t m = 0; m < members.size(); ++m)
-                cur[m] = best[members[m]];
-            float best_ms = 0.f;
-            st = time_set(members, cur, &best_ms);
-            std::vector<z4c_launch> pick = cur;
-            for (int pers : {0, 1, 2}) {
-                if (st != Z4C_OK)
-                    break;
-                std::vector<z4c_launch> uni(members.size(), cur[0]);
-                for (auto &L : uni)
-                    L.persistent = pers * P->num_cus;
-                float ms = 0.f;
-                st = time_set(members, uni, &ms);
-                if (st == Z4C_OK && ms < 0.985f * best_ms) {
-                    best_ms = ms;
-                    pick = uni;
-                }
-            }
+            (void)hipEventElapsedTime(&ms, e0, e1);
+            (void)hipEventDestroy(e0);
+            (void)hipEventDestroy(e1);
             if (st != Z4C_OK)
-                break;
-            for (size_t m = 0; m < members.size(); ++m) {
-                const size_t ci = members[m];
-                if (pick[m].persistent != best[ci].persistent)
-                    best_time[ci] = best_ms / reps;   // now a member of a merged dispatch
-                best[ci] = pick[m];
-            }
+                return st;
         }
+        fresh = true;
+        c.launch = own;
+        cache.entries[key] = TuneEntry{own, ms / reps};
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    P->classes = saved;
-    if (st == Z4C_OK) {
-        bool fresh = false;
-        for (size_t ci = 0; ci < saved.size(); ++ci) {
-            P->classes[ci].launch = best[ci];
-            if (best_time[ci] >= 0.f) {
-                cache.entries[keys[ci]] = TuneEntry{best[ci], best_time[ci]};
-                fresh = true;
-            }
-        }
-        if (fresh)
-            tune_cache_store(cache);
-    }
-    const z4c_status st2 = build_groups(P);
-    return st != Z4C_OK ? st : st2;
+    count_tiles(P);
+    if (fresh)
+        tune_cache_store(cache);
+    HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    return Z4C_OK;
 }
 
 z4c_status z4c_set_tune_cache(const char *path)

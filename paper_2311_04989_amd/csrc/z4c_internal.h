@@ -23,9 +23,17 @@ enum ConsField : int { C_H = 0, C_MX, C_MY, C_MZ, C_THETA, C_ZX, C_ZY, C_ZZ, NCO
 // What a tile kernel produces.
 enum Mode : int { MODE_RHS = 0, MODE_RK = 1, MODE_CONS = 2, MODE_RK_MON = 3 };
 
-// One work item of a tile kernel: block index and interior origin of the tile.
+// One work item of a tile kernel: block index and interior origin of the tile
+// (TILE_X x TILE_Y x TILE_Z points, whatever launch shape the caller names).
+constexpr int TILE_X = 8, TILE_Y = 8, TILE_Z = 4;
 struct Tile {
     int block, i0, j0, k0;
+};
+
+// Coefficients of a Runge-Kutta stage as the tile kernels read them.
+struct RKArgs {
+    double delta, eps_dt, g1, g2, g3, beta_dt;
+    int read_u1, write_u1, use_u2, u2_is_u0;
 };
 
 struct StageArgs {
@@ -34,9 +42,6 @@ struct StageArgs {
     const float *fac32;      // the same factors rounded to float
     const Tile *tiles;
     int ntiles;
-    int persistent;          // 0: one workgroup per tile; else that many workgroups
-    int *queue;              // persistent: 8 tile counters (one per XCD range), zeroed
-    long long tile_base;     // global index of tiles[0] (norm partial sums)
     const double *u;         // input state (u0 for a stage)
     const double *matter;    // nullptr = vacuum
     double *out;             // rhs, u0_out, or constraint fields (may be nullptr for CONS)
@@ -44,9 +49,7 @@ struct StageArgs {
     const double *u2;
     double *partial;         // CONS: per-tile sums, [tile][16]
     double *cons;            // RK_MON: constraint fields of the input (may be nullptr)
-    // Runge-Kutta stage
-    double delta, eps_dt, g1, g2, g3, beta_dt;
-    int read_u1, write_u1, use_u2, u2_is_u0;
+    RKArgs rk;
     // scheme
     double ko_sigma, kappa1, kappa2, eta, chi_floor, alpha_floor;
     int lapse, shift, advect_gauge;
@@ -104,27 +107,22 @@ struct RadiativeArgs {
 // (60, 180) for order 6, r = order/2 + 1.
 void block_factors(const z4c_block &b, int fd_order, double sigma, double out[12]);
 
-// Launch entry points implemented in z4c_kernels.hip (tile kernels: one
-// variant per order, arithmetic, tile shape and occupancy target `waves`
-// = waves per SIMD the kernel is compiled for).
-hipError_t launch_stage(int mode, int fd_order, int arith, int tx, int ty, int tz, int waves,
-                        const StageArgs &a, hipStream_t s);
-bool stage_shape_supported(int fd_order, int tx, int ty, int tz, int waves);
-hipError_t launch_p6_f64(int mode, int tx, int ty, int tz, int w, const StageArgs &a,
-                         hipStream_t s);
-hipError_t launch_p6_f32(int mode, int tx, int ty, int tz, int w, const StageArgs &a,
-                         hipStream_t s);
-hipError_t launch_p4(int mode, int arith, int tx, int ty, int tz, int w, const StageArgs &a,
-                     hipStream_t s);
-// Right-hand side / stage with lopsided advection (FP64, z4c_variants_lop.hip).
-hipError_t launch_lopsided(int mode, int fd_order, int tx, int ty, int tz, int w,
-                           const StageArgs &a, hipStream_t s);
-// Naive-FP32 right-hand side (z4c_variants_naive.hip).
-hipError_t launch_naive(int fd_order, int tx, int ty, int tz, int w, const StageArgs &a,
+// Tile-kernel launches (z4c_kernels.hip): what `mode` produces with the
+// scheme's order, arithmetic and advection.
+hipError_t launch_stage(int mode, int fd_order, int arith, int advection, const StageArgs &a,
                         hipStream_t s);
+// Launch shapes that z4c_plan_set_launch takes.
+bool stage_shape_supported(int fd_order, int tx, int ty, int tz, int waves);
+// One translation unit per kernel family (z4c_variants_*.hip).
+hipError_t launch_p6_f64(int mode, const StageArgs &a, hipStream_t s);
+hipError_t launch_p6_f32(int mode, const StageArgs &a, hipStream_t s);
+hipError_t launch_p4(int mode, int arith, const StageArgs &a, hipStream_t s);
+// Right-hand side / stage with lopsided advection (FP64, z4c_variants_lop.hip).
+hipError_t launch_lopsided(int mode, int fd_order, const StageArgs &a, hipStream_t s);
+// Naive-FP32 right-hand side, order 6 (z4c_variants_naive.hip).
+hipError_t launch_naive(const StageArgs &a, hipStream_t s);
 // Stage with the constraint monitor (FP64, z4c_variants_mon.hip).
-hipError_t launch_monitor(int fd_order, int tx, int ty, int tz, int w, const StageArgs &a,
-                          hipStream_t s);
+hipError_t launch_monitor(int fd_order, const StageArgs &a, hipStream_t s);
 hipError_t launch_ghost(const GhostArgs &g, long long total_ghost, hipStream_t s);
 // Radiative outer boundary (z4c_boundary.hip).
 hipError_t launch_radiative(const RadiativeArgs &a, hipStream_t s);
@@ -135,10 +133,6 @@ hipError_t launch_finite_count(const z4c_block *blocks, int nblocks, const long 
                                long long total_pts, const double *u,
                                unsigned long long *count, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long *p, hipStream_t s);
-// Zero the 8 tile counters of a persistent launch (a kernel, so that captured
-// graphs replay it).
-hipError_t launch_zero_queue(int *q, hipStream_t s);
-
 // Read access to a plan from other translation units: its host block table,
 // its device copy (nullptr without a device).
 const std::vector<z4c_block> &plan_blocks(const z4c_plan *P);

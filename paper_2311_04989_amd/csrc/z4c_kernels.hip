@@ -143,18 +143,10 @@ __global__ void finite_count_kernel(const z4c_block *blocks, int nblocks, const 
 
 __global__ void zero_u64_kernel(unsigned long long *p) { *p = 0ull; }
 
-__global__ void zero_queue_kernel(int *q)
-{
-    if (threadIdx.x < 8)
-        q[threadIdx.x] = 0;
-}
-
 }  // namespace
 
 bool stage_shape_supported(int fd_order, int tx, int ty, int tz, int waves)
 {
-    // one wave per SIMD (a 256-register budget plus as many accumulation
-    // registers): 256-point tiles 8x8x4 and 8x4x8 of the order-6 kernels
     if (tx == 8 && ty == 4 && tz == 8)
         return waves == 1 && fd_order == 6;
     if (tx != 8 || ty != 8 || (tz != 8 && tz != 4))
@@ -162,19 +154,22 @@ bool stage_shape_supported(int fd_order, int tx, int ty, int tz, int waves)
     return waves == 2 || (waves == 1 && tz == 4 && fd_order == 6);
 }
 
-hipError_t launch_stage(int mode, int fd_order, int arith, int tx, int ty, int tz, int waves,
-                        const StageArgs &a, hipStream_t s)
+hipError_t launch_stage(int mode, int fd_order, int arith, int advection, const StageArgs &a,
+                        hipStream_t s)
 {
+    if (a.ntiles <= 0)
+        return hipSuccess;
     if (mode == MODE_RK_MON)
-        return launch_monitor(fd_order, tx, ty, tz, waves, a, s);
+        return launch_monitor(fd_order, a, s);
+    if (mode != MODE_CONS && advection == Z4C_ADVECT_LOPSIDED)
+        return launch_lopsided(mode, fd_order, a, s);
     if (arith == Z4C_ARITH_FP32_NAIVE && mode != MODE_CONS)
-        return mode == MODE_RHS ? launch_naive(fd_order, tx, ty, tz, waves, a, s)
-                                : hipErrorInvalidValue;
+        return mode == MODE_RHS ? launch_naive(a, s) : hipErrorInvalidValue;
     if (fd_order == 4)
-        return launch_p4(mode, arith, tx, ty, tz, waves, a, s);
+        return launch_p4(mode, arith, a, s);
     if (mode == MODE_CONS || arith != Z4C_ARITH_FP32)
-        return launch_p6_f64(mode, tx, ty, tz, waves, a, s);
-    return launch_p6_f32(mode, tx, ty, tz, waves, a, s);
+        return launch_p6_f64(mode, a, s);
+    return launch_p6_f32(mode, a, s);
 }
 
 hipError_t launch_ghost(const GhostArgs &g, long long total_ghost, hipStream_t s)
@@ -205,12 +200,6 @@ hipError_t launch_finite_count(const z4c_block *blocks, int nblocks, const long 
     const long long nb = (total_pts + 255) / 256;
     finite_count_kernel<<<dim3((unsigned)nb), dim3(256), 0, s>>>(blocks, nblocks, pt_start,
                                                                 total_pts, u, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_queue(int *q, hipStream_t s)
-{
-    zero_queue_kernel<<<1, 64, 0, s>>>(q);
     return hipGetLastError();
 }
 
