@@ -6,171 +6,6 @@
 namespace z4c {
 namespace tile {
 
-// Staging by z-columns.  The halo box of a tile is LX x LY columns of LZ
-// points; thread t holds the whole column (t mod LX, t / LX) of a field in
-// registers.  What the stencils read of it goes to LDS: the x and y stencils
-// need the TZ interior planes (PLN doubles each, rows PX apart), the z
-// stencils only the TX x TY interior columns (NZC doubles, planes TX * TY
-// apart), and the z sums of the mixed derivatives are formed from the
-// registers.  That is 18 KB per field and tile instead of the whole box's
-// 37 KB, and a field without second derivatives loads 1,280 points instead
-// of 3,072.  With the sums and 25 values per thread parked in LDS, a
-// workgroup takes half a CU's LDS and its lanes half a SIMD's registers
-// without scratch: two workgroups per CU, whose barriers and memory waits
-// cover one another.
-template <int P, int TX, int TY, int TZ>
-struct ColDims {
-    static constexpr int RAD = P / 2 + 1, Q = P / 2, NT = TX * TY * TZ;
-    static constexpr int LX = TX + 2 * RAD, LY = TY + 2 * RAD, LZ = TZ + 2 * RAD;
-    static constexpr int PX = pad_pitch(LX), PLN = PX * LY;
-    static constexpr int NPL = PLN * TZ, NZC = TX * TY * LZ;
-    static_assert(LX * LY <= NT, "one column per thread");
-    static_assert(TZ >= RAD, "at most the first tile of a block reaches below it");
-};
-
-// Fields with second derivatives.
-__host__ __device__ constexpr bool mixed_field(int f)
-{
-    return f == CHI || f == ALPHA || (f >= GXX && f <= GZZ) || (f >= BETAX && f <= BETAZ);
-}
-
-// The column of one thread and where its points come from.  The refresh rule
-// acts per direction, so the source of a point is the column's (x, y) part,
-// fixed per thread, plus the plane's z part, the same for all threads: a
-// byte offset per plane in scalar registers.
-// GEN (frozen and neighbour rules): the array and block that the (x, y) part
-// refers to depend on whether the plane lies below, in or above the block,
-// so a thread keeps one pointer for each (`below`, `in`, `above`).
-template <int P, int TX, int TY, int TZ, bool GEN>
-struct ColStager {
-    using D = ColDims<P, TX, TY, TZ>;
-    double pf[D::LZ];
-    unsigned zo[D::LZ];                    // byte offset of plane q (uniform)
-    const double *own;                     // field 0 of the block (uniform)
-    long long fs;
-    unsigned xy;                           // !GEN: byte offset of the column within a plane
-    const double *below, *in, *above;      // GEN
-    int qa;                                // GEN: first plane above the block (uniform)
-    // interior column; column the z sums read; column of the x or y stencils
-    bool ca, cb, cf;
-
-    __device__ __forceinline__ void setup(const StageArgs &a, const Tile &T, const z4c_block &B,
-                                          unsigned t)
-    {
-        const int cx = t % D::LX, cy = t / D::LX, ng = B.ng;
-        const int sy = B.nx + 2 * ng, sz = sy * (B.ny + 2 * ng);
-        const bool inx = cx >= D::RAD && cx < D::RAD + TX, iny = cy >= D::RAD && cy < D::RAD + TY;
-        ca = inx && iny;
-        cb = cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
-        cf = (inx || iny) && cy < D::LY;
-        own = a.u + B.offset;
-        fs = B.field_stride;
-        // ragged tiles: points beyond the stored region are clamped into it
-        // (no active point's stencil reaches them)
-        int gi = T.i0 - D::RAD + cx, gj = T.j0 - D::RAD + cy;
-        gi = gi < B.nx + ng ? gi : B.nx + ng - 1;
-        gj = gj < B.ny + ng ? gj : B.ny + ng - 1;
-        const int ox = gi < 0 ? -1 : (gi >= B.nx ? 1 : 0);
-        const int oy = gj < 0 ? -1 : (gj >= B.ny ? 1 : 0);
-        const int wi = gi - ox * B.nx, wj = gj - oy * B.ny;   // wrapped
-        const bool wrap = GEN || a.halo == Z4C_GHOST_PERIODIC;
-#pragma unroll
-        for (int q = 0; q < D::LZ; ++q) {
-            int gk = T.k0 - D::RAD + q;
-            gk = gk < B.nz + ng ? gk : B.nz + ng - 1;
-            if (wrap)
-                gk = gk < 0 ? gk + B.nz : (gk >= B.nz ? gk - B.nz : gk);
-            zo[q] = 8u * (unsigned)((gk + ng) * sz);
-        }
-        const int stored = (gj + ng) * sy + gi + ng, wrapped = (wj + ng) * sy + wi + ng;
-        if constexpr (!GEN) {
-            xy = 8u * (unsigned)(wrap ? wrapped : stored);
-        } else {
-            auto source = [&](int oz) __attribute__((always_inline)) {
-                if ((ox | oy | oz) == 0)
-                    return own + stored;
-                const int sb = a.halo == Z4C_GHOST_NEIGHBOUR
-                    ? a.nbr[T.block * 27 + (oz + 1) * 9 + (oy + 1) * 3 + (ox + 1)] : -1;
-                if (sb >= 0)   // same nx, ny, nz, ng and field stride as this block
-                    return a.u + a.blocks[sb].offset + wrapped;
-                // frozen, or the stored ghost that a refresh leaves as it is;
-                // the plane offsets are wrapped ones
-                return (a.frozen ? a.frozen + B.offset : own) + stored + (long long)(oz * B.nz) * sz;
-            };
-            in = source(0);
-            below = T.k0 == 0 ? source(-1) : in;
-            above = source(1);
-            qa = B.nz - T.k0 + D::RAD;
-        }
-    }
-    // Requests the points of field f that its stencils read.
-    template <bool MIX>
-    __device__ __forceinline__ void prefetch(int f)
-    {
-        auto load = [&](auto ld) __attribute__((always_inline)) {
-            if (MIX ? (cb || cf) : cf) {
-#pragma unroll
-                for (int q = D::RAD; q < D::RAD + TZ; ++q)
-                    ld(q);
-            }
-            if (MIX ? cb : ca) {
-#pragma unroll
-                for (int q = 1; q < D::RAD; ++q) {
-                    ld(q);
-                    ld(D::LZ - 1 - q);
-                }
-            }
-            if (ca) {
-                ld(0);
-                ld(D::LZ - 1);
-            }
-        };
-        if constexpr (GEN) {
-            const long long fo = f * fs * 8;
-            load([&](int q) __attribute__((always_inline)) {
-                const double *p = q < D::RAD ? below : (q < qa ? in : above);
-                pf[q] = *(const gdouble *)((const __attribute__((address_space(1))) char *)p
-                                           + (fo + zo[q]));
-            });
-        } else {
-            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(own + (long long)f * fs), 0, -1, 0x00027000);
-            load([&](int q) __attribute__((always_inline)) {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, xy, zo[q], 0);
-                pf[q] = __builtin_bit_cast(double, v);
-            });
-        }
-    }
-};
-
-// First and second derivative and dissipation along one axis: the centre
-// value and the taps c[0], c[ST], .. c[2 RAD ST] (centre at RAD ST).
-template <int P, typename R, int ST>
-__device__ __forceinline__ void axis(const double *c, double c0, R f1, R f2, R fk, R &d1, R &d2,
-                                     R &ko)
-{
-    constexpr int RAD = P / 2 + 1;
-    double p[5], m[5];
-#pragma unroll
-    for (int q = 1; q <= RAD; ++q) {
-        p[q] = c[(RAD + q) * ST];
-        m[q] = c[(RAD - q) * ST];
-    }
-    const double s1 = (p[1] - c0) + (m[1] - c0), s2 = (p[2] - c0) + (m[2] - c0),
-                 s3 = (p[3] - c0) + (m[3] - c0);
-    if constexpr (P == 4) {
-        d1 = (R(8) * R(p[1] - m[1]) - R(p[2] - m[2])) * f1;
-        d2 = (R(16) * R(s1) - R(s2)) * f2;
-        ko = (R(15) * R(s1) - R(6) * R(s2) + R(s3)) * fk;
-    } else {
-        const double s4 = (p[4] - c0) + (m[4] - c0);
-        d1 = (R(45) * R(p[1] - m[1]) - R(9) * R(p[2] - m[2]) + R(p[3] - m[3])) * f1;
-        d2 = (R(270) * R(s1) - R(27) * R(s2) + R(2) * R(s3)) * f2;
-        ko = (-R(56) * R(s1) + R(28) * R(s2) - R(8) * R(s3) + R(s4)) * fk;
-    }
-}
-
 // Lopsided first derivative along one axis, unscaled (same 1/(c1 h) factor
 // as the centred one): the order-P stencil on the points shifted by one
 // towards the side `pos` (offsets -P/2+1 .. P/2+1 when pos, mirrored
@@ -229,7 +64,7 @@ stage_kernel(const StageArgs a)
 {
     using D = ColDims<P, TX, TY, TZ>;
     using MZ = MixDimsZ<P, TX, TY, TZ>;
-    constexpr int RAD = D::RAD, NT = D::NT;
+    constexpr int NT = D::NT;
     constexpr bool RK = MODE == MODE_RK;
     // plane part, interior columns, z and y sums of the staged field
     __shared__ double pl[D::NPL];
@@ -303,96 +138,22 @@ stage_kernel(const StageArgs a)
         const Fac<R> F = table_entry(sizeof(R) == sizeof(double) ? (const Fac<R> *)a.fac64
                                                                  : (const Fac<R> *)a.fac32,
                                      T.block);
-        ColStager<P, TX, TY, TZ, GEN> st;
-        st.setup(a, T, B, t);
-        // LDS offsets of this thread (opaque, so that they are kept and not
-        // formed again for each field): its column in pl, zc and zs; the
-        // lower corner of its x / y taps in pl and its row of y taps there
-        // (y sums); where its y sum goes; its z and y sums
-        const unsigned cx = t % D::LX, cy = t / D::LX;
-        const unsigned sx = t % 16, sr = t / 16, ry = sr % TY, rz = sr / TY;
-        unsigned pcol = cy * D::PX + cx, zcol = (cy - RAD) * TX + (cx - RAD);
-        unsigned zrow = ((cy - 1) & 1) * MZ::ZR::OFF + ((cy - 1) >> 1) * 16 + cx - 1;
-        unsigned po0 = tz * D::PLN + ty * D::PX + tx;
-        unsigned ysrc = rz * D::PLN + (ry + RAD) * D::PX + sx + (RAD - MZ::Q);
-        unsigned ydst = rz * MZ::YR::PLANE + (ry & 1) * MZ::YR::OFF + (ry >> 1) * 16 + sx;
-        const unsigned r0 = ty + MZ::Q, r1 = r0 + 1;
-        unsigned pz = tz * MZ::ZR::PLANE + (r0 & 1) * MZ::ZR::OFF + (r0 >> 1) * 16 + tx + MZ::Q;
-        unsigned pz1 = tz * MZ::ZR::PLANE + (r1 & 1) * MZ::ZR::OFF + (r1 >> 1) * 16 + tx + MZ::Q;
-        unsigned py = tz * MZ::YR::PLANE + (ty & 1) * MZ::YR::OFF + (ty >> 1) * 16 + tx + MZ::Q;
-        asm volatile("" : "+v"(pcol), "+v"(zcol), "+v"(zrow), "+v"(po0), "+v"(ysrc), "+v"(ydst));
-        asm volatile("" : "+v"(pz), "+v"(pz1), "+v"(py));
-        unsigned po = po0, zo = t;
+        FieldTile<P, TX, TY, TZ, GEN> ft;
+        ft.setup(a, T, B, t, pl, zc, zs, ys);
         // Stages field FF and requests the next one.
         auto stage = [&](auto FC) __attribute__((always_inline)) {
             constexpr int FF = decltype(FC)::value;
-            constexpr int NX = next_field<MODE>(FF);
-            constexpr bool MIX = mixed_field(FF);
-            __syncthreads();
-            if constexpr (NAIVE) {
-#pragma unroll
-                for (int q = 0; q < D::LZ; ++q)
-                    st.pf[q] = double(float(st.pf[q]));
-            }
-            if (MIX ? (st.cb || st.cf) : st.cf) {
-#pragma unroll
-                for (int z = 0; z < TZ; ++z)
-                    pl[z * D::PLN + pcol] = st.pf[RAD + z];
-            }
-            if (st.ca) {
-#pragma unroll
-                for (int q = 0; q < D::LZ; ++q)
-                    zc[q * TX * TY + zcol] = st.pf[q];
-            }
-            if constexpr (MIX) {
-                if (st.cb) {
-#pragma unroll
-                    for (int z = 0; z < TZ; ++z)
-                        zs[z * MZ::ZR::PLANE + zrow] = d1raw<P, double, 1>(st.pf + z + RAD);
-                }
-            }
-            if constexpr (NX >= 0)
-                st.template prefetch<mixed_field(NX)>(NX);
-            __syncthreads();
-            if constexpr (MIX) {
-                // y sums: 16 threads per row (those past EX idle)
-                constexpr int NE = 16 * TY * TZ, DZ = NT / (16 * TY);
-                static_assert(NE % NT == 0 && NT % (16 * TY) == 0, "whole planes per pass");
-                if (sx < MZ::EX) {
-#pragma unroll
-                    for (int q = 0; q < NE / NT; ++q)
-                        ys[ydst + q * DZ * MZ::YR::PLANE] =
-                            d1raw<P, double, D::PX>(pl + ysrc + q * DZ * D::PLN);
-                }
-                __syncthreads();
-            }
-            po = po0;
-            zo = t;
-            asm volatile("" : "+v"(po), "+v"(zo));   // tap addresses anew for each field
+            ft.template stage<FF, next_field<MODE>(FF), NAIVE>();
         };
-        st.template prefetch<mixed_field(BETAX)>(BETAX);
-
-        // State value of the field staged in LDS at this thread's point.
-        auto staged = [&]() __attribute__((always_inline)) { return pl[po + RAD * D::PX + RAD]; };
-        // First derivatives, pure second derivatives and dissipation of the
-        // staged field.
-        auto pure = [&](R d[3], R &xx, R &yy, R &zz, R &ko) __attribute__((always_inline)) {
-            const double c0 = staged();
-            R kx, ky, kz;
-            axis<P, R, 1>(pl + po + RAD * D::PX, c0, F.d1[0], F.d2[0], F.ko[0], d[0], xx, kx);
-            axis<P, R, D::PX>(pl + po + RAD, c0, F.d1[1], F.d2[1], F.ko[1], d[1], yy, ky);
-            axis<P, R, TX * TY>(zc + zo, c0, F.d1[2], F.d2[2], F.ko[2], d[2], zz, kz);
-            ko = kx + ky + kz;
-        };
+        ft.st.template prefetch<mixed_field(BETAX)>(BETAX);
+        auto staged = [&]() __attribute__((always_inline)) { return ft.centre(); };
         auto derivs1 = [&](R d[3], R &ko) __attribute__((always_inline)) {
             R xx, yy, zz;
-            pure(d, xx, yy, zz, ko);
+            ft.pure(F, d, xx, yy, zz, ko);
         };
         auto derivs2 = [&](R d[3], R dd[6], R &ko) __attribute__((always_inline)) {
-            pure(d, dd[0], dd[3], dd[5], ko);
-            dd[1] = R(d1sum<P, double, 1>(ys + py)) * F.mix[0];
-            dd[2] = R(d1sum<P, double, 1>(zs + pz)) * F.mix[1];
-            dd[4] = R(d1sum_rows<P, double>(zs + pz, zs + pz1)) * F.mix[2];
+            ft.pure(F, d, dd[0], dd[3], dd[5], ko);
+            ft.mixed(F, dd);
         };
         auto centre = [&](int f) __attribute__((always_inline)) {
             return active ? R(at(ub + f * fs, upt8)) : R(0);
@@ -440,9 +201,9 @@ stage_kernel(const StageArgs a)
         auto adv = [&](const R d[3]) __attribute__((always_inline)) {
             if constexpr (LOP) {
                 const double c0 = staged();
-                return beta[0] * (lopc<P, R, 1>(pl + po + RAD * D::PX, c0, beta[0] > R(0)) * F.d1[0])
-                     + beta[1] * (lopc<P, R, D::PX>(pl + po + RAD, c0, beta[1] > R(0)) * F.d1[1])
-                     + beta[2] * (lopc<P, R, TX * TY>(zc + zo, c0, beta[2] > R(0)) * F.d1[2]);
+                return beta[0] * (lopc<P, R, 1>(ft.xtaps(), c0, beta[0] > R(0)) * F.d1[0])
+                     + beta[1] * (lopc<P, R, D::PX>(ft.ytaps(), c0, beta[1] > R(0)) * F.d1[1])
+                     + beta[2] * (lopc<P, R, TX * TY>(ft.ztaps(), c0, beta[2] > R(0)) * F.d1[2]);
             } else {
                 return beta[0] * d[0] + beta[1] * d[1] + beta[2] * d[2];
             }
@@ -941,13 +702,6 @@ stage_kernel(const StageArgs a)
 }
 
 }  // namespace tile
-
-// Launches: halo sources beyond the block itself only under the frozen and
-// neighbour rules.
-inline bool general_halo(const StageArgs &a)
-{
-    return a.halo == Z4C_GHOST_FROZEN || a.halo == Z4C_GHOST_NEIGHBOUR;
-}
 
 // MODE_RHS or MODE_RK; WPE: waves per SIMD the kernel is compiled for.
 template <int P, int WPE, typename R, int MODE, bool MON = false, bool LOP = false,

@@ -70,62 +70,10 @@ __device__ __forceinline__ R d1raw(const double *c)
     }
 }
 
-template <int P, typename R, int ST>
-__device__ __forceinline__ R d2raw(const double *c)
-{
-    const double c0 = c[0];
-    if constexpr (P == 4) {
-        return R(16) * R((c[ST] - c0) + (c[-ST] - c0))
-               - R((c[2 * ST] - c0) + (c[-2 * ST] - c0));
-    } else {
-        return R(270) * R((c[ST] - c0) + (c[-ST] - c0))
-               - R(27) * R((c[2 * ST] - c0) + (c[-2 * ST] - c0))
-               + R(2) * R((c[3 * ST] - c0) + (c[-3 * ST] - c0));
-    }
-}
-
 template <typename R>
 struct Fac {
     R d1[3], d2[3], mix[3], ko[3];   // mix: xy, xz, yz
 };
-
-// Mixed second derivatives in two passes, x/y first (the constraint
-// kernel's form; the stage kernel's z-first form follows): every
-// thread first writes unscaled x- and y-first-derivative sums of the staged
-// field over the tile extended by the stencil half width in the other
-// directions (x sums: y and z extended; y sums: z extended); after a
-// barrier, d_x d_y, d_x d_z and d_y d_z are first-derivative stencils on
-// those sums (the tensor-product stencil).
-template <int P, int TX, int TY, int TZ>
-struct MixDims {
-    static constexpr int Q = P / 2;
-    static constexpr int DY = TY + 2 * Q, DZ = TZ + 2 * Q;
-    static constexpr int NXS = TX * DY * DZ;   // x sums
-    static constexpr int NYS = TX * TY * DZ;   // y sums
-};
-
-template <int P, typename R, int TX, int TY, int TZ, int PX, int PXY>
-__device__ __forceinline__ void mix_prep(const double *L, R *dxb, R *dyb, int t)
-{
-    using M = MixDims<P, TX, TY, TZ>;
-    constexpr int NT = TX * TY * TZ, RAD = P / 2 + 1, Q = M::Q;
-#pragma unroll
-    for (int q = 0; q < (M::NXS + NT - 1) / NT; ++q) {
-        const int e = t + q * NT;
-        if ((q + 1) * NT <= M::NXS || e < M::NXS) {
-            const int ex = e % TX, r = e / TX, ey = r % M::DY, ez = r / M::DY;
-            dxb[e] = d1raw<P, R, 1>(L + (ez - Q + RAD) * PXY + (ey - Q + RAD) * PX + (ex + RAD));
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < (M::NYS + NT - 1) / NT; ++q) {
-        const int e = t + q * NT;
-        if ((q + 1) * NT <= M::NYS || e < M::NYS) {
-            const int ex = e % TX, r = e / TX, ey = r % TY, ez = r / TY;
-            dyb[e] = d1raw<P, R, PX>(L + (ez - Q + RAD) * PXY + (ey + RAD) * PX + (ex + RAD));
-        }
-    }
-}
 
 template <int P, typename R, int ST>
 __device__ __forceinline__ R d1sum(const R *c)
@@ -173,32 +121,6 @@ __device__ __forceinline__ R d1sum_rows(const R *pe, const R *po)
         return R(8) * (po[0] - po[-16]) - (pe[16] - pe[-16]);
     else
         return R(45) * (po[0] - po[-16]) - R(9) * (pe[16] - pe[-16]) + (po[16] - po[-32]);
-}
-
-// Unfused helpers used by the constraint kernel.
-template <int P, typename R, int PX, int PXY>
-__device__ __forceinline__ void first(const double *c, const Fac<R> &F, R d[3])
-{
-    d[0] = d1raw<P, R, 1>(c) * F.d1[0];
-    d[1] = d1raw<P, R, PX>(c) * F.d1[1];
-    d[2] = d1raw<P, R, PXY>(c) * F.d1[2];
-}
-
-// Second derivatives, the mixed ones from the two-pass sums of mix_prep
-// (dxb, dyb).
-template <int P, typename R, int PX, int PXY, int TX, int TY, int TZ>
-__device__ __forceinline__ void second_sums(const double *c, const Fac<R> &F, R dd[6],
-                                            const R *dxb, const R *dyb, int tx, int ty, int tz)
-{
-    using M = MixDims<P, TX, TY, TZ>;
-    dd[0] = d2raw<P, R, 1>(c) * F.d2[0];
-    dd[3] = d2raw<P, R, PX>(c) * F.d2[1];
-    dd[5] = d2raw<P, R, PXY>(c) * F.d2[2];
-    const R *px = dxb + ((tz + M::Q) * M::DY + (ty + M::Q)) * TX + tx;
-    const R *py = dyb + ((tz + M::Q) * TY + ty) * TX + tx;
-    dd[1] = d1sum<P, R, TX>(px) * F.mix[0];
-    dd[2] = d1sum<P, R, TX * M::DY>(px) * F.mix[1];
-    dd[4] = d1sum<P, R, TX * TY>(py) * F.mix[2];
 }
 
 template <typename R>
@@ -275,37 +197,24 @@ __device__ __forceinline__ void sfor(Fn &&f)
     sfor_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// Field staged after field f (-1: none).  Constraints: gt, Gt, chi, Khat,
-// Theta, At.  Right-hand side / stage: beta, gt, Gt, alpha, chi, Khat,
+// Field staged after field f (-1: none).  Constraints: chi, gt, Gt, Khat,
+// Theta, At.  Right-hand side / stage: beta, gt, Gt, lapse, chi, Khat,
 // Theta, At.
 template <int MODE>
 __host__ __device__ constexpr int next_field(int f)
 {
-    if (MODE != MODE_CONS) {
-        if (f == BETAX || f == BETAY)
-            return f + 1;
-        if (f == BETAZ)
-            return GXX;
+    constexpr bool CONS = MODE == MODE_CONS;
+    switch (f) {
+    case BETAZ: return GXX;
+    case GZZ: return GAMX;
+    case GAMZ: return CONS ? KHAT : ALPHA;
+    case ALPHA: return CHI;
+    case CHI: return CONS ? GXX : KHAT;
+    case KHAT: return THETA;
+    case THETA: return AXX;
+    case AZZ: return -1;
+    default: return f + 1;   // components of one tensor
     }
-    if (f >= GXX && f < GZZ)
-        return f + 1;
-    if (f == GZZ)
-        return GAMX;
-    if (f == GAMX || f == GAMY)
-        return f + 1;
-    if (f == GAMZ)
-        return MODE == MODE_CONS ? CHI : ALPHA;
-    if (f == ALPHA)
-        return CHI;
-    if (f == CHI)
-        return KHAT;
-    if (f == KHAT)
-        return THETA;
-    if (f == THETA)
-        return AXX;
-    if (f >= AXX && f < AZZ)
-        return f + 1;
-    return -1;
 }
 
 // Element at byte offset `boff` from a (wave-uniform) base in global memory: a
@@ -342,372 +251,297 @@ __device__ __forceinline__ T table_entry(const T *p, long long n)
     return read_words<T>(
         (const __attribute__((address_space(4))) unsigned *)(unsigned long long)(p + n));
 }
-// Halo-tile staging of one field at a time: registers <- HBM (prefetch of
-// the next field), LDS <- registers (between two barriers).  Each halo
-// element has a 32-bit element offset found once per tile: from the block's
-// own base of field 0 for its own points and stored ghosts, the periodic
-// image and the same point of `frozen`; from the state array base for
-// another block's point under the neighbour rule (the plan refuses that rule
-// unless such offsets stay below 2^32).  Blocks of the first kind may lie
-// anywhere in the state array.
-template <int NLD>
-struct Stager {
-    int ldo[NLD];
-    unsigned src[NLD];
-    unsigned valid, frz, far;   // bit q: element q is loaded / from `frozen` / from another block
-    double pf[NLD];
-    const double *own, *own_frozen, *all;   // u + offset, frozen + offset, u
-    long long fs;
+// Staging by z-columns.  The halo box of a tile is LX x LY columns of LZ
+// points; thread t holds the whole column (t mod LX, t / LX) of a field in
+// registers.  What the stencils read of it goes to LDS: the x and y stencils
+// need the TZ interior planes (PLN doubles each, rows PX apart), the z
+// stencils only the TX x TY interior columns (NZC doubles, planes TX * TY
+// apart), and the z sums of the mixed derivatives are formed from the
+// registers.  That is 18 KB per field and tile instead of the whole box's
+// 37 KB, and a field without second derivatives loads 1,280 points instead
+// of 3,072.  With the sums and 25 values per thread parked in LDS, a
+// workgroup takes half a CU's LDS and its lanes half a SIMD's registers
+// without scratch: two workgroups per CU, whose barriers and memory waits
+// cover one another.
+template <int P, int TX, int TY, int TZ>
+struct ColDims {
+    static constexpr int RAD = P / 2 + 1, Q = P / 2, NT = TX * TY * TZ;
+    static constexpr int LX = TX + 2 * RAD, LY = TY + 2 * RAD, LZ = TZ + 2 * RAD;
+    static constexpr int PX = pad_pitch(LX), PLN = PX * LY;
+    static constexpr int NPL = PLN * TZ, NZC = TX * TY * LZ;
+    static_assert(LX * LY <= NT, "one column per thread");
+    static_assert(TZ >= RAD, "at most the first tile of a block reaches below it");
+};
 
+// Fields with second derivatives.
+__host__ __device__ constexpr bool mixed_field(int f)
+{
+    return f == CHI || f == ALPHA || (f >= GXX && f <= GZZ) || (f >= BETAX && f <= BETAZ);
+}
+
+// The column of one thread and where its points come from.  The refresh rule
+// acts per direction, so the source of a point is the column's (x, y) part,
+// fixed per thread, plus the plane's z part, the same for all threads: a
+// byte offset per plane in scalar registers.
+// GEN (frozen and neighbour rules): the array and block that the (x, y) part
+// refers to depend on whether the plane lies below, in or above the block,
+// so a thread keeps one pointer for each (`below`, `in`, `above`).
+template <int P, int TX, int TY, int TZ, bool GEN>
+struct ColStager {
+    using D = ColDims<P, TX, TY, TZ>;
+    double pf[D::LZ];
+    unsigned zo[D::LZ];                    // byte offset of plane q (uniform)
+    const double *own;                     // field 0 of the block (uniform)
+    long long fs;
+    unsigned xy;                           // !GEN: byte offset of the column within a plane
+    const double *below, *in, *above;      // GEN
+    int qa;                                // GEN: first plane above the block (uniform)
+    // interior column; column the z sums read; column of the x or y stencils
+    bool ca, cb, cf;
+
+    __device__ __forceinline__ void setup(const StageArgs &a, const Tile &T, const z4c_block &B,
+                                          unsigned t)
+    {
+        const int cx = t % D::LX, cy = t / D::LX, ng = B.ng;
+        const int sy = B.nx + 2 * ng, sz = sy * (B.ny + 2 * ng);
+        const bool inx = cx >= D::RAD && cx < D::RAD + TX, iny = cy >= D::RAD && cy < D::RAD + TY;
+        ca = inx && iny;
+        cb = cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
+        cf = (inx || iny) && cy < D::LY;
+        own = a.u + B.offset;
+        fs = B.field_stride;
+        // ragged tiles: points beyond the stored region are clamped into it
+        // (no active point's stencil reaches them)
+        int gi = T.i0 - D::RAD + cx, gj = T.j0 - D::RAD + cy;
+        gi = gi < B.nx + ng ? gi : B.nx + ng - 1;
+        gj = gj < B.ny + ng ? gj : B.ny + ng - 1;
+        const int ox = gi < 0 ? -1 : (gi >= B.nx ? 1 : 0);
+        const int oy = gj < 0 ? -1 : (gj >= B.ny ? 1 : 0);
+        const int wi = gi - ox * B.nx, wj = gj - oy * B.ny;   // wrapped
+        const bool wrap = GEN || a.halo == Z4C_GHOST_PERIODIC;
+#pragma unroll
+        for (int q = 0; q < D::LZ; ++q) {
+            int gk = T.k0 - D::RAD + q;
+            gk = gk < B.nz + ng ? gk : B.nz + ng - 1;
+            if (wrap)
+                gk = gk < 0 ? gk + B.nz : (gk >= B.nz ? gk - B.nz : gk);
+            zo[q] = 8u * (unsigned)((gk + ng) * sz);
+        }
+        const int stored = (gj + ng) * sy + gi + ng, wrapped = (wj + ng) * sy + wi + ng;
+        if constexpr (!GEN) {
+            xy = 8u * (unsigned)(wrap ? wrapped : stored);
+        } else {
+            auto source = [&](int oz) __attribute__((always_inline)) {
+                if ((ox | oy | oz) == 0)
+                    return own + stored;
+                const int sb = a.halo == Z4C_GHOST_NEIGHBOUR
+                    ? a.nbr[T.block * 27 + (oz + 1) * 9 + (oy + 1) * 3 + (ox + 1)] : -1;
+                if (sb >= 0)   // same nx, ny, nz, ng and field stride as this block
+                    return a.u + a.blocks[sb].offset + wrapped;
+                // frozen, or the stored ghost that a refresh leaves as it is;
+                // the plane offsets are wrapped ones
+                return (a.frozen ? a.frozen + B.offset : own) + stored + (long long)(oz * B.nz) * sz;
+            };
+            in = source(0);
+            below = T.k0 == 0 ? source(-1) : in;
+            above = source(1);
+            qa = B.nz - T.k0 + D::RAD;
+        }
+    }
+    // Requests the points of field f that its stencils read.
+    template <bool MIX>
     __device__ __forceinline__ void prefetch(int f)
     {
-        const long long e = (long long)f * fs;   // uniform
+        auto load = [&](auto ld) __attribute__((always_inline)) {
+            if (MIX ? (cb || cf) : cf) {
 #pragma unroll
-        for (int q = 0; q < NLD; ++q)
-            pf[q] = (valid >> q) & 1u
-                        ? ((far >> q) & 1u ? all + e : (frz >> q) & 1u ? own_frozen + e : own + e)[src[q]]
-                        : 0.0;
-    }
-    __device__ __forceinline__ void store(double *lds)
-    {
+                for (int q = D::RAD; q < D::RAD + TZ; ++q)
+                    ld(q);
+            }
+            if (MIX ? cb : ca) {
 #pragma unroll
-        for (int q = 0; q < NLD; ++q)
-            if (ldo[q] >= 0)
-                lds[ldo[q]] = pf[q];
+                for (int q = 1; q < D::RAD; ++q) {
+                    ld(q);
+                    ld(D::LZ - 1 - q);
+                }
+            }
+            if (ca) {
+                ld(0);
+                ld(D::LZ - 1);
+            }
+        };
+        if constexpr (GEN) {
+            const long long fo = f * fs * 8;
+            load([&](int q) __attribute__((always_inline)) {
+                const double *p = q < D::RAD ? below : (q < qa ? in : above);
+                pf[q] = *(const gdouble *)((const __attribute__((address_space(1))) char *)p
+                                           + (fo + zo[q]));
+            });
+        } else {
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(own + (long long)f * fs), 0, -1, 0x00027000);
+            load([&](int q) __attribute__((always_inline)) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, xy, zo[q], 0);
+                pf[q] = __builtin_bit_cast(double, v);
+            });
+        }
     }
 };
 
-template <int NLD, int NT, int RAD, int LX, int LY, int LZ, int PX, int PXY>
-__device__ __forceinline__ void setup_stager(Stager<NLD> &st, const StageArgs &a, const Tile &T,
-                                             const z4c_block &B, int t)
-{
-    constexpr int LVOL = LX * LY * LZ;
-    const int ng = B.ng;
-    const int sy = B.nx + 2 * ng;
-    const int sz = sy * (B.ny + 2 * ng);
-    st.own = a.u + B.offset;
-    st.own_frozen = a.frozen ? a.frozen + B.offset : nullptr;
-    st.all = a.u;
-    st.fs = B.field_stride;
-    st.valid = 0u;
-    st.frz = 0u;
-    st.far = 0u;
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-        const int e = t + q * NT;
-        st.ldo[q] = -1;
-        st.src[q] = 0u;
-        if (e < LVOL) {
-            const int lx = e % LX, r1 = e / LX, ly = r1 % LY, lz = r1 / LY;
-            const int gi = T.i0 - RAD + lx, gj = T.j0 - RAD + ly, gk = T.k0 - RAD + lz;
-            st.ldo[q] = lz * PXY + ly * PX + lx;
-            if (gi >= -ng && gi < B.nx + ng && gj >= -ng && gj < B.ny + ng && gk >= -ng
-                && gk < B.nz + ng) {
-                const int ox = gi < 0 ? -1 : (gi >= B.nx ? 1 : 0);
-                const int oy = gj < 0 ? -1 : (gj >= B.ny ? 1 : 0);
-                const int oz = gk < 0 ? -1 : (gk >= B.nz ? 1 : 0);
-                unsigned idx = (unsigned)((gk + ng) * sz + (gj + ng) * sy + (gi + ng));
-                if ((ox | oy | oz) != 0 && a.halo != Z4C_GHOST_NONE) {
-                    int sb = -1;
-                    if (a.halo == Z4C_GHOST_PERIODIC)
-                        sb = T.block;
-                    else if (a.halo == Z4C_GHOST_NEIGHBOUR)
-                        sb = a.nbr[T.block * 27 + (oz + 1) * 9 + (oy + 1) * 3 + (ox + 1)];
-                    if (sb >= 0) {
-                        // same nx, ny, nz, ng and field stride as this block
-                        const int si = gi - ox * B.nx, sj = gj - oy * B.ny, sk = gk - oz * B.nz;
-                        idx = (unsigned)((sk + ng) * sz + (sj + ng) * sy + (si + ng));
-                        if (sb != T.block) {
-                            idx += (unsigned)a.blocks[sb].offset;
-                            st.far |= 1u << q;
-                        }
-                    } else if (a.frozen) {
-                        st.frz |= 1u << q;
-                    }   // else: the stored ghost, which a refresh leaves as it is
-                }
-                st.src[q] = idx;
-                st.valid |= 1u << q;
-            }
-        }
-    }
-}
-
-template <int P, int TX, int TY, int TZ, typename R>
-__global__ void __launch_bounds__(TX *TY *TZ) cons_kernel(const StageArgs a)
+// First and second derivative and dissipation along one axis: the centre
+// value and the taps c[0], c[ST], .. c[2 RAD ST] (centre at RAD ST).
+template <int P, typename R, int ST>
+__device__ __forceinline__ void axis(const double *c, double c0, R f1, R f2, R fk, R &d1, R &d2,
+                                     R &ko)
 {
     constexpr int RAD = P / 2 + 1;
-    constexpr int NT = TX * TY * TZ;
-    constexpr int LX = TX + 2 * RAD, LY = TY + 2 * RAD, LZ = TZ + 2 * RAD;
-    constexpr int PX = pad_pitch(LX);
-    constexpr int PXY = PX * LY;
-    constexpr int LVOL = LX * LY * LZ;
-    constexpr int NLD = (LVOL + NT - 1) / NT;
-    __shared__ double lds[PXY * LZ];
-    __shared__ double red[(NT / 64) * 16];
-    // mixed second derivatives of chi and gt in two passes (as the stage
-    // kernel): x and y first-derivative sums here
-    using MD = MixDims<P, TX, TY, TZ>;
-    __shared__ R dxb[MD::NXS];
-    __shared__ R dyb[MD::NYS];
-
-    const int t = threadIdx.x;
-    const int tx = t % TX, ty = (t / TX) % TY, tz = t / (TX * TY);
-    const double *lc = lds + (tz + RAD) * PXY + (ty + RAD) * PX + (tx + RAD);
-
-    {
-        const int tile = my_tile();
-        const Tile T = a.tiles[tile];
-        const z4c_block B = a.blocks[T.block];
-        const int ng = B.ng;
-        const int sy = B.nx + 2 * ng;
-        const int sz = sy * (B.ny + 2 * ng);
-        const int i = T.i0 + tx, j = T.j0 + ty, k = T.k0 + tz;
-        const bool active = i < B.nx && j < B.ny && k < B.nz;
-        const int pt = (k + ng) * sz + (j + ng) * sy + (i + ng);
-        const double *ub = a.u + B.offset;
-        const long long fs = B.field_stride;
-
-        Stager<NLD> st;
-        setup_stager<NLD, NT, RAD, LX, LY, LZ, PX, PXY>(st, a, T, B, t);
-        auto stage = [&](auto FC) __attribute__((always_inline)) {
-            constexpr int FF = decltype(FC)::value;
-            constexpr int NX = next_field<MODE_CONS>(FF);
-            __syncthreads();
-            st.store(lds);
-            if constexpr (NX >= 0)
-                st.prefetch(NX);
-            __syncthreads();
-            if constexpr (FF == CHI || (FF >= GXX && FF <= GZZ)) {
-                mix_prep<P, R, TX, TY, TZ, PX, PXY>(lds, dxb, dyb, t);
-                __syncthreads();
-            }
-        };
-
-        st.prefetch(GXX);
-
-        const Fac<R> F = table_entry((const Fac<R> *)a.fac64, T.block);
-        // Conformal metric, its inverse; conformal factor.
-        R g[6];
-        sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { g[q] = active ? R(ub[(GXX + q) * fs + pt]) : ((q == 0 || q == 3 || q == 5) ? R(1) : R(0)); } });
-        R gi[6];
-        {
-            const R det = g[0] * (g[3] * g[5] - g[4] * g[4]) - g[1] * (g[1] * g[5] - g[4] * g[2])
-                        + g[2] * (g[1] * g[4] - g[3] * g[2]);
-            const R id = R(1) / det;
-            gi[0] = (g[3] * g[5] - g[4] * g[4]) * id;
-            gi[1] = (g[2] * g[4] - g[1] * g[5]) * id;
-            gi[2] = (g[1] * g[4] - g[2] * g[3]) * id;
-            gi[3] = (g[0] * g[5] - g[2] * g[2]) * id;
-            gi[4] = (g[2] * g[1] - g[0] * g[4]) * id;
-            gi[5] = (g[0] * g[3] - g[1] * g[1]) * id;
-        }
-        const R chi = active ? R(ub[CHI * fs + pt]) : R(1);
-        const R chis = chi > R(a.chi_floor) ? chi : R(a.chi_floor);
-        const R ichi2 = R(0.5) / chis;          // 1 / (2 chi)
-        R cons[NCONS];
-        sfor<NCONS>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { cons[q] = R(0); } });
-
-        // ---- conformal metric: d gt, d d gt -> Rt_ij (second-derivative part)
-        R dg[3][6];
-        R Rij[6];
-        sfor<6>([&](auto Q) __attribute__((always_inline)) {
-            constexpr int q = decltype(Q)::value;
-            stage(std::integral_constant<int, GXX + q>{});
-            if (active) {
-                R d[3], dd[6];
-                first<P, R, PX, PXY>(lc, F, d);
-                second_sums<P, R, PX, PXY, TX, TY, TZ>(lc, F, dd, dxb, dyb, tx, ty, tz);
-                sfor<3>([&](auto kk_c) __attribute__((always_inline)) { constexpr int kk = decltype(kk_c)::value; { dg[kk][q] = d[kk]; } });
-                Rij[q] = R(-0.5) * symtrace(gi, dd);
-            }
-        });
-
-        // Christoffel symbols: Gl[k][ij] = Gt_{k ij}, Gu[k][ij] = Gt^k_{ij}, Gd^i.
-        R Gu[3][6], Gd[3];
-        if (active) {
-            R Gl[3][6];
-            sfor<3>([&](auto kk_c) __attribute__((always_inline)) { constexpr int kk = decltype(kk_c)::value; {                 sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-                    const int ii = SI(q), jj = SJ(q);
-                    Gl[kk][q] = R(0.5) * (dg[ii][S(jj, kk)] + dg[jj][S(ii, kk)] - dg[kk][q]);
-                } }); } });
-            sfor<3>([&](auto kk_c) __attribute__((always_inline)) { constexpr int kk = decltype(kk_c)::value; {                 sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { Gu[kk][q] = gi[S(kk, 0)] * Gl[0][q] + gi[S(kk, 1)] * Gl[1][q]
-                              + gi[S(kk, 2)] * Gl[2][q]; } }); } });
-            sfor<3>([&](auto ii_c) __attribute__((always_inline)) { constexpr int ii = decltype(ii_c)::value; { Gd[ii] = symtrace(gi, Gu[ii]); } });
-            // Rt_ij += 1/2 Gd^k (Gt_{ijk} + Gt_{jik})
-            //        + sum_kl (Gu^k_{li} T_{jk}^l + Gu^k_{lj} T_{ik}^l + Gu^k_{il} T_{kj}^l),
-            // T_{ab}^c = gt^{cm} Gt_{a bm}
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-                const int ii = SI(q), jj = SJ(q);
-                R s = R(0);
-                sfor<3>([&](auto kk_c) __attribute__((always_inline)) { constexpr int kk = decltype(kk_c)::value; { s += R(0.5) * Gd[kk] * (Gl[ii][S(jj, kk)] + Gl[jj][S(ii, kk)]); } });
-                Rij[q] += s;
-            } });
-            sfor<3>([&](auto p0_c) __attribute__((always_inline)) { constexpr int p0 = decltype(p0_c)::value; {                 sfor<3>([&](auto p1_c) __attribute__((always_inline)) { constexpr int p1 = decltype(p1_c)::value; {
-                    R Tc[3];
-                    sfor<3>([&](auto p2_c) __attribute__((always_inline)) { constexpr int p2 = decltype(p2_c)::value; { Tc[p2] = gi[S(p2, 0)] * Gl[p0][S(p1, 0)] + gi[S(p2, 1)] * Gl[p0][S(p1, 1)]
-                               + gi[S(p2, 2)] * Gl[p0][S(p1, 2)]; } });
-                    // T_{p0 p1}^{l}: contributes as T_{jk}^l (j=p0, k=p1),
-                    // T_{ik}^l (i=p0, k=p1) and T_{kj}^l (k=p0, j=p1)
-                    sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-                        const int ii = SI(q), jj = SJ(q);
-                        R s = R(0);
-                        sfor<3>([&](auto l_c) __attribute__((always_inline)) { constexpr int l = decltype(l_c)::value; {
-                            if (jj == p0)
-                                s += Gu[p1][S(l, ii)] * Tc[l];
-                            if (ii == p0)
-                                s += Gu[p1][S(l, jj)] * Tc[l];
-                            if (jj == p1)
-                                s += Gu[p0][S(ii, l)] * Tc[l];
-                        } });
-                        Rij[q] += s;
-                    } });
-                } }); } });
-        }
-
-        // ---- Gamma-tilde: d_j Gt^k -> Rt_ij; damping; Z^i
-        sfor<3>([&](auto KK) __attribute__((always_inline)) {
-            constexpr int kk = decltype(KK)::value;
-            stage(std::integral_constant<int, GAMX + kk>{});
-            if (active) {
-                R d[3];
-                first<P, R, PX, PXY>(lc, F, d);
-                sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-                    const int ii = SI(q), jj = SJ(q);
-                    Rij[q] += R(0.5) * (g[S(kk, ii)] * d[jj] + g[S(kk, jj)] * d[ii]);
-                } });
-                const R Gam = R(lc[0]);
-                cons[C_ZX + kk] = R(0.5) * (Gam - Gd[kk]);
-            }
-        });
-
-        // ---- chi: R^chi_ij
-        R dchi[3];
-        stage(std::integral_constant<int, CHI>{});
-        if (active) {
-            R dd[6];
-            first<P, R, PX, PXY>(lc, F, dchi);
-            second_sums<P, R, PX, PXY, TX, TY, TZ>(lc, F, dd, dxb, dyb, tx, ty, tz);
-            R DD[6];
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { DD[q] = dd[q] - (Gu[0][q] * dchi[0] + Gu[1][q] * dchi[1] + Gu[2][q] * dchi[2]); } });
-            const R trDD = symtrace(gi, DD);
-            R dc2[6];
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { dc2[q] = dchi[SI(q)] * dchi[SJ(q)]; } });
-            const R dchi2 = symtrace(gi, dc2);
-            const R i4c2 = ichi2 * ichi2;   // 1 / (4 chi^2)
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { Rij[q] += (DD[q] + g[q] * trDD) * ichi2 - (dc2[q] + R(3) * g[q] * dchi2) * i4c2; } });
-        }
-
-        // ---- Khat, Theta (their Gamma-tilde source terms)
-        R KT[2];
-        sfor<2>([&](auto Q) __attribute__((always_inline)) {
-            constexpr int q = decltype(Q)::value;
-            stage(std::integral_constant<int, q == 0 ? KHAT : THETA>{});
-            if (active) {
-                R d[3];
-                first<P, R, PX, PXY>(lc, F, d);
-                KT[q] = R(lc[0]);
-                const R c = q == 0 ? R(-2.0 / 3.0) : R(-4.0 / 3.0);
-                sfor<3>([&](auto ii_c) __attribute__((always_inline)) { constexpr int ii = decltype(ii_c)::value; { cons[C_MX + ii] += c * d[ii]; } });
-            }
-        });
-
-        // ---- pointwise algebra
-        R A[6];
-        if (active) {
-            const R Khat = KT[0], Theta = KT[1];
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { A[q] = R(ub[(AXX + q) * fs + pt]); } });
-            R rho = R(0), Si[3] = {R(0), R(0), R(0)}, Sij[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
-            if (a.matter) {
-                const double *mb = a.matter + B.moffset;
-                rho = R(mb[pt]);
-                sfor<3>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { Si[q] = R(mb[(1 + q) * fs + pt]); } });
-                sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { Sij[q] = R(mb[(4 + q) * fs + pt]); } });
-            }
-            // At^i_j and At^{ij}
-            R Amix[3][3];
-            sfor<3>([&](auto ii_c) __attribute__((always_inline)) { constexpr int ii = decltype(ii_c)::value; {                 sfor<3>([&](auto jj_c) __attribute__((always_inline)) { constexpr int jj = decltype(jj_c)::value; { Amix[ii][jj] = gi[S(ii, 0)] * A[S(0, jj)] + gi[S(ii, 1)] * A[S(1, jj)]
-                                 + gi[S(ii, 2)] * A[S(2, jj)]; } }); } });
-            R Aup[6];
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-                const int ii = SI(q), jj = SJ(q);
-                Aup[q] = Amix[ii][0] * gi[S(0, jj)] + Amix[ii][1] * gi[S(1, jj)]
-                       + Amix[ii][2] * gi[S(2, jj)];
-            } });
-            R AA = R(0);
-            sfor<6>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { AA += R(SW(q)) * A[q] * Aup[q]; } });
-            const R K = Khat + R(2) * Theta;
-            const R Rs = chi * symtrace(gi, Rij);
-            const R pi = R(PI);
-            cons[C_H] = Rs + R(2.0 / 3.0) * K * K - AA - R(16) * pi * rho;
-            cons[C_THETA] = Theta;
-            sfor<3>([&](auto ii_c) __attribute__((always_inline)) { constexpr int ii = decltype(ii_c)::value; {
-                R s = R(0);
-                sfor<3>([&](auto jj_c) __attribute__((always_inline)) { constexpr int jj = decltype(jj_c)::value; {                         sfor<3>([&](auto kk_c) __attribute__((always_inline)) { constexpr int kk = decltype(kk_c)::value; {
-                        R c2 = R(0);
-                        sfor<3>([&](auto l_c) __attribute__((always_inline)) { constexpr int l = decltype(l_c)::value; { c2 += Gu[l][S(jj, kk)] * A[S(l, ii)] + Gu[l][S(jj, ii)] * A[S(kk, l)]; } });
-                        s += gi[S(jj, kk)] * c2;
-                    } }); } });
-                const R Ac = Amix[0][ii] * dchi[0] + Amix[1][ii] * dchi[1]
-                           + Amix[2][ii] * dchi[2];
-                cons[C_MX + ii] += -s - R(1.5) / chis * Ac - R(8) * pi * Si[ii];
-            } });
-        }
-
-        // ---- At_ij
-        sfor<6>([&](auto Q) __attribute__((always_inline)) {
-            constexpr int q = decltype(Q)::value;
-            stage(std::integral_constant<int, AXX + q>{});
-            if (active) {
-                R d[3];
-                first<P, R, PX, PXY>(lc, F, d);
-                constexpr int ii = SI(q), jj = SJ(q);
-                cons[C_MX + ii] += gi[S(jj, 0)] * d[0] + gi[S(jj, 1)] * d[1] + gi[S(jj, 2)] * d[2];
-                if constexpr (ii != jj)
-                    cons[C_MX + jj] += gi[S(ii, 0)] * d[0] + gi[S(ii, 1)] * d[1]
-                                     + gi[S(ii, 2)] * d[2];
-            }
-        });
-
-        // ---- output
-        if (active && a.out) {
-            double *cb = a.out + B.coffset;
-            sfor<NCONS>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { cb[q * fs + pt] = double(cons[q]); } });
-        }
-        // Per-tile sums of |c| and c^2 in a fixed order: wave reduction,
-        // then the waves in order.
-        double v[16];
-        sfor<NCONS>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
-            const double c = active ? double(cons[q]) : 0.0;
-            v[2 * q] = fabs(c);
-            v[2 * q + 1] = c * c;
-        } });
-        sfor<16>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; {
+    double p[5], m[5];
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1)
-                v[q] += __shfl_xor(v[q], off, 64);
-        } });
-        const int wave = t >> 6, lane = t & 63;
-        __syncthreads();
-        if (lane == 0)
-            sfor<16>([&](auto q_c) __attribute__((always_inline)) { constexpr int q = decltype(q_c)::value; { red[wave * 16 + q] = v[q]; } });
-        __syncthreads();
-        if (t < 16) {
-            double s = 0.0;
-            for (int w = 0; w < NT / 64; ++w)
-                s += red[w * 16 + t];
-            a.partial[tile * 16LL + t] = s;
-        }
+    for (int q = 1; q <= RAD; ++q) {
+        p[q] = c[(RAD + q) * ST];
+        m[q] = c[(RAD - q) * ST];
+    }
+    const double s1 = (p[1] - c0) + (m[1] - c0), s2 = (p[2] - c0) + (m[2] - c0),
+                 s3 = (p[3] - c0) + (m[3] - c0);
+    if constexpr (P == 4) {
+        d1 = (R(8) * R(p[1] - m[1]) - R(p[2] - m[2])) * f1;
+        d2 = (R(16) * R(s1) - R(s2)) * f2;
+        ko = (R(15) * R(s1) - R(6) * R(s2) + R(s3)) * fk;
+    } else {
+        const double s4 = (p[4] - c0) + (m[4] - c0);
+        d1 = (R(45) * R(p[1] - m[1]) - R(9) * R(p[2] - m[2]) + R(p[3] - m[3])) * f1;
+        d2 = (R(270) * R(s1) - R(27) * R(s2) + R(2) * R(s3)) * f2;
+        ko = (-R(56) * R(s1) + R(28) * R(s2) - R(8) * R(s3) + R(s4)) * fk;
     }
 }
+
+// The staged field of a tile in LDS and this thread's view of it.
+template <int P, int TX, int TY, int TZ, bool GEN>
+struct FieldTile {
+    using D = ColDims<P, TX, TY, TZ>;
+    using MZ = MixDimsZ<P, TX, TY, TZ>;
+    ColStager<P, TX, TY, TZ, GEN> st;
+    double *pl, *zc, *zs, *ys;      // plane part, interior columns, z and y sums
+    // LDS offsets of this thread (opaque to the compiler, so that they are
+    // kept and not formed again for each field): its column in pl, zc and zs;
+    // the lower corner of its x / y taps in pl and its row of y taps there (y
+    // sums); where its y sum goes; its z and y sums
+    unsigned t, pcol, zcol, zrow, po0, ysrc, ydst, pz, pz1, py;
+    unsigned po, zo;                // taps in pl and zc, anew for each field
+    bool ysum;
+
+    __device__ __forceinline__ void setup(const StageArgs &a, const Tile &T, const z4c_block &B,
+                                          unsigned thread, double *pl_, double *zc_, double *zs_,
+                                          double *ys_)
+    {
+        t = thread;
+        pl = pl_;
+        zc = zc_;
+        zs = zs_;
+        ys = ys_;
+        st.setup(a, T, B, t);
+        const unsigned tx = t % TX, ty = (t / TX) % TY, tz = t / (TX * TY);
+        const unsigned cx = t % D::LX, cy = t / D::LX;
+        const unsigned sx = t % 16, sr = t / 16, ry = sr % TY, rz = sr / TY;
+        pcol = cy * D::PX + cx;
+        zcol = (cy - D::RAD) * TX + (cx - D::RAD);
+        zrow = ((cy - 1) & 1) * MZ::ZR::OFF + ((cy - 1) >> 1) * 16 + cx - 1;
+        po0 = tz * D::PLN + ty * D::PX + tx;
+        ysum = sx < MZ::EX;
+        ysrc = rz * D::PLN + (ry + D::RAD) * D::PX + sx + (D::RAD - MZ::Q);
+        ydst = rz * MZ::YR::PLANE + (ry & 1) * MZ::YR::OFF + (ry >> 1) * 16 + sx;
+        const unsigned r0 = ty + MZ::Q, r1 = r0 + 1;
+        pz = tz * MZ::ZR::PLANE + (r0 & 1) * MZ::ZR::OFF + (r0 >> 1) * 16 + tx + MZ::Q;
+        pz1 = tz * MZ::ZR::PLANE + (r1 & 1) * MZ::ZR::OFF + (r1 >> 1) * 16 + tx + MZ::Q;
+        py = tz * MZ::YR::PLANE + (ty & 1) * MZ::YR::OFF + (ty >> 1) * 16 + tx + MZ::Q;
+        asm volatile("" : "+v"(pcol), "+v"(zcol), "+v"(zrow), "+v"(po0), "+v"(ysrc), "+v"(ydst));
+        asm volatile("" : "+v"(pz), "+v"(pz1), "+v"(py));
+        po = po0;
+        zo = t;
+    }
+    // Puts the requested field FF into LDS and requests field NX (-1: none).
+    template <int FF, int NX, bool NAIVE = false>
+    __device__ __forceinline__ void stage()
+    {
+        constexpr bool MIX = mixed_field(FF);
+        __syncthreads();
+        if constexpr (NAIVE) {
+#pragma unroll
+            for (int q = 0; q < D::LZ; ++q)
+                st.pf[q] = double(float(st.pf[q]));
+        }
+        if (MIX ? (st.cb || st.cf) : st.cf) {
+#pragma unroll
+            for (int z = 0; z < TZ; ++z)
+                pl[z * D::PLN + pcol] = st.pf[D::RAD + z];
+        }
+        if (st.ca) {
+#pragma unroll
+            for (int q = 0; q < D::LZ; ++q)
+                zc[q * TX * TY + zcol] = st.pf[q];
+        }
+        if constexpr (MIX) {
+            if (st.cb) {
+#pragma unroll
+                for (int z = 0; z < TZ; ++z)
+                    zs[z * MZ::ZR::PLANE + zrow] = d1raw<P, double, 1>(st.pf + z + D::RAD);
+            }
+        }
+        if constexpr (NX >= 0)
+            st.template prefetch<mixed_field(NX)>(NX);
+        __syncthreads();
+        if constexpr (MIX) {
+            // y sums: 16 threads per row (those past EX idle)
+            constexpr int NE = 16 * TY * TZ, DZ = D::NT / (16 * TY);
+            static_assert(NE % D::NT == 0 && D::NT % (16 * TY) == 0, "whole planes per pass");
+            if (ysum) {
+#pragma unroll
+                for (int q = 0; q < NE / D::NT; ++q)
+                    ys[ydst + q * DZ * MZ::YR::PLANE] =
+                        d1raw<P, double, D::PX>(pl + ysrc + q * DZ * D::PLN);
+            }
+            __syncthreads();
+        }
+        po = po0;
+        zo = t;
+        asm volatile("" : "+v"(po), "+v"(zo));
+    }
+    // lowest taps of this thread's stencils, centre at RAD strides
+    __device__ __forceinline__ const double *xtaps() const { return pl + po + D::RAD * D::PX; }
+    __device__ __forceinline__ const double *ytaps() const { return pl + po + D::RAD; }
+    __device__ __forceinline__ const double *ztaps() const { return zc + zo; }
+    // value of the staged field at this thread's point
+    __device__ __forceinline__ double centre() const { return pl[po + D::RAD * D::PX + D::RAD]; }
+    // First and pure second derivatives and dissipation of the staged field.
+    template <typename R>
+    __device__ __forceinline__ void pure(const Fac<R> &F, R d[3], R &xx, R &yy, R &zz, R &ko) const
+    {
+        const double c0 = centre();
+        R kx, ky, kz;
+        axis<P, R, 1>(xtaps(), c0, F.d1[0], F.d2[0], F.ko[0], d[0], xx, kx);
+        axis<P, R, D::PX>(ytaps(), c0, F.d1[1], F.d2[1], F.ko[1], d[1], yy, ky);
+        axis<P, R, TX * TY>(ztaps(), c0, F.d1[2], F.d2[2], F.ko[2], d[2], zz, kz);
+        ko = kx + ky + kz;
+    }
+    // Mixed second derivatives, from the sums (formed in double also for
+    // float arithmetic: a difference of rounded sums would lose digits).
+    template <typename R>
+    __device__ __forceinline__ void mixed(const Fac<R> &F, R dd[6]) const
+    {
+        dd[1] = R(d1sum<P, double, 1>(ys + py)) * F.mix[0];
+        dd[2] = R(d1sum<P, double, 1>(zs + pz)) * F.mix[1];
+        dd[4] = R(d1sum_rows<P, double>(zs + pz, zs + pz1)) * F.mix[2];
+    }
+};
 
 }  // namespace tile
 
-template <int P>
-hipError_t launch_cons(const StageArgs &a, hipStream_t s)
+// Launches: halo sources beyond the block itself only under the frozen and
+// neighbour rules.
+inline bool general_halo(const StageArgs &a)
 {
-    tile::cons_kernel<P, TILE_X, TILE_Y, TILE_Z, double>
-        <<<a.ntiles, dim3(TILE_X * TILE_Y * TILE_Z), 0, s>>>(a);
-    return hipGetLastError();
+    return a.halo == Z4C_GHOST_FROZEN || a.halo == Z4C_GHOST_NEIGHBOUR;
 }
 
 }  // namespace z4c

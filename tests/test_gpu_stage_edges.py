@@ -80,11 +80,18 @@ def test_tile_edges(order, n, rule):
         m = dev(bt.matter)
         plan.rhs(u, m, rhs)
         plan.rk_stage(u, out, acc, u, m, Z.RK4[1], 0.01)
+        cons = torch.zeros(bt.total_c, dtype=torch.float64, device="cuda:0")
+        norms = torch.zeros(16 * len(bt.blocks), dtype=torch.float64, device="cuda:0")
+        plan.constraints(u, m, cons, norms)
         torch.cuda.synchronize()
-        got[read] = (rhs.cpu().numpy(), out.cpu().numpy(), acc.cpu().numpy())
+        got[read] = [x.cpu().numpy() for x in (rhs, out, acc, cons, norms)]
         plan.close()
     for a, b in zip(got["rule"], got["stored"]):
         assert np.array_equal(a, b)
     bt.u = filled
     rows = compare(bt, got["stored"][0], O.rhs(bt), O.rhs(bt, ext=True))
     assert_parity(rows, f"tile edges {order} {n} {rule}\n" + report(rows))
+    c80, n80 = O.constraints(bt, ext=True)
+    rows = compare(bt, got["stored"][3], O.constraints(bt)[0], c80, nfields=W.NC)
+    assert_parity(rows, f"tile edges {order} {n} {rule} constraints\n" + report(rows))
+    np.testing.assert_allclose(got["stored"][4].reshape(-1, 8, 2), n80, rtol=1e-10, atol=1e-300)
