@@ -128,9 +128,10 @@ z4c_status z4c_sources_to_vc(const z4c_mplan *plan, int order, const double *adm
  *   - otherwise the inversion is the root in mu = 1 / (h W) of the master
  *     function of Kastaun, Kalinani & Ciolfi (the algorithm the paper's
  *     primitive solver is based on): bracketed in [0, mu+] (mu+ from their
- *     auxiliary function), Illinois iterations to a relative width `tol` or
- *     `max_iter` iterations; no sign change or no convergence: atmosphere
- *     (status 3);
+ *     auxiliary function), Newton steps held in the bracket until one is
+ *     below max(tol, 1e-9) relative, and where that takes too long Illinois
+ *     iterations to a relative width `tol`, each at most `max_iter`; no sign
+ *     change or no convergence: atmosphere (status 3);
  *   - a solution with |ut| = sqrt(W^2 - 1) above ut_max (the velocity
  *     ceiling), or with rho < f_thr rho_atm, becomes atmosphere (status 2 /
  *     status 1);
