@@ -42,9 +42,13 @@ __device__ __forceinline__ R lopc(const double *c, double c0, bool pos)
 // What bounds it: latency (barriers, LDS round trips, HBM) and, with two
 // workgroups per CU, about equally HBM traffic.  Measured against the kernel
 // with the whole box in LDS and one workgroup per CU (256 points each
-// way): RK4 stage 2 of 512 blocks of 16^3 1.371 -> 1.026 ms (3.6 TB/s of HBM
-// traffic), RK4 step of 1,024 uneven blocks 18.3 -> 13.5 ms, of 8 x 128^3
-// blocks with matter 48.3 -> 31.3 ms.  With every load served from one block
+// way): RK4 stage 2 of 512 blocks of 16^3 1.371 -> 1.004 ms (3.7 TB/s of HBM
+// traffic), RK4 step of 1,024 uneven blocks 18.3 -> 13.2 ms, of 8 x 128^3
+// blocks with matter 48.3 -> 30.7 ms.  Of this 3 % come from the wait for the
+// next field's points before a field's stores (1.036, 13.5, 31.3 ms without):
+// the stores then drain behind the next field instead of in front of it.
+// Non-temporal stores are slower (1.15 ms): the 64-byte row pieces of x
+// neighbours no longer meet in L2.  With every load served from one block
 // (L2) the 512-block stage takes 0.63 ms.  A loop over tiles (work queue) in
 // this kernel keeps per-tile values live across tiles and spills: 1.31 ms.
 // Tiles of 8x8x8 (512 threads, one workgroup per CU): 1.04 ms; requesting u1
@@ -158,23 +162,29 @@ stage_kernel(const StageArgs a)
         auto centre = [&](int f) __attribute__((always_inline)) {
             return active ? R(at(ub + f * fs, upt8)) : R(0);
         };
-        // Runge-Kutta combination of field f (state u0) with right-hand side kf (FP64).
-        auto combine = [&](int f, R kf_r, double u0, const Old &o) __attribute__((always_inline)) {
+        // Values to store: the field (or its right-hand side) and its u1 register.
+        struct New {
+            double w, n1;
+        };
+        // Runge-Kutta combination of a field (state u0) with right-hand side kf (FP64).
+        auto combine = [&](R kf_r, double u0, const Old &o) __attribute__((always_inline)) {
             const double kf = double(kf_r);
+            if constexpr (!RK)
+                return New{kf, 0.0};
             const double n1 = o.u1 + a.rk.delta * u0 + a.rk.eps_dt * kf;
             double w = a.rk.g1 * u0 + a.rk.g2 * n1;
             if (a.rk.use_u2)
                 w += a.rk.g3 * (a.rk.u2_is_u0 ? u0 : o.u2);
-            if (a.rk.write_u1)
-                at(u1b + f * fs, upt8) = n1;
-            return w + a.rk.beta_dt * kf;
+            return New{w + a.rk.beta_dt * kf, n1};
         };
-        // Finish a field that needs no enforcement.
-        auto finish = [&](int f, R kf, double u0, const Old &o) __attribute__((always_inline)) {
+        auto write1 = [&](int f, const New &v) __attribute__((always_inline)) {
             if constexpr (RK)
-                at(ob + f * fs, upt8) = combine(f, kf, u0, o);
-            else
-                at(ob + f * fs, upt8) = double(kf);
+                if (a.rk.write_u1)
+                    at(u1b + f * fs, upt8) = v.n1;
+        };
+        auto write = [&](int f, const New &v) __attribute__((always_inline)) {
+            write1(f, v);
+            at(ob + f * fs, upt8) = v.w;
         };
 
         R g[6];
@@ -236,6 +246,7 @@ stage_kernel(const StageArgs a)
         sfor<3>([&](auto K_c) __attribute__((always_inline)) {
             constexpr int kk = decltype(K_c)::value;
             stage(std::integral_constant<int, BETAX + kk>{});
+            New nw;
             if (active) {
                 const Old o = old(BETAX + kk);
                 const R Gam = R(at(ub + (GAMX + kk) * fs, upt8));
@@ -254,8 +265,11 @@ stage_kernel(const StageArgs a)
                 });
                 const R kb = (a.advect_gauge ? adv(d) : R(0)) + ko
                            + (a.shift == Z4C_SHIFT_GAMMADRIVER ? Gam : R(0)) - R(a.eta) * beta[kk];
-                finish(BETAX + kk, kb, staged(), o);
+                nw = combine(kb, staged(), o);
             }
+            ft.arrive();
+            if (active)
+                write(BETAX + kk, nw);
         });
 
         // ---- conformal metric
@@ -266,6 +280,7 @@ stage_kernel(const StageArgs a)
             constexpr int q = decltype(Q_c)::value;
             constexpr int ii = SI(q), jj = SJ(q);
             stage(std::integral_constant<int, GXX + q>{});
+            New nw;
             if (active) {
                 const Old o = old(GXX + q);
                 const R Aq = R(at(ub + (AXX + q) * fs, upt8));
@@ -283,10 +298,16 @@ stage_kernel(const StageArgs a)
                 });
                 const R kg = adv(d) + ko - R(2) * alpha * Aq + lie
                            - R(2.0 / 3.0) * g[q] * divb;
-                if constexpr (RK)
-                    vg[q] = combine(GXX + q, kg, staged(), o);
-                else
-                    at(ob + (GXX + q) * fs, upt8) = double(kg);
+                nw = combine(kg, staged(), o);
+            }
+            ft.arrive();
+            if (active) {
+                if constexpr (RK) {
+                    vg[q] = nw.w;
+                    write1(GXX + q, nw);
+                } else {
+                    write(GXX + q, nw);
+                }
             }
         });
         if constexpr (RK) {
@@ -403,6 +424,7 @@ stage_kernel(const StageArgs a)
         R dal[3], DDa[6];
         R Khat = R(0);
         stage(std::integral_constant<int, ALPHA>{});
+        New nal;
         if (active) {
             const Old o = old(ALPHA);
             Khat = R(at(ub + KHAT * fs, upt8));
@@ -419,13 +441,13 @@ stage_kernel(const StageArgs a)
                 muL = alpha * alpha;
             const R ka = (a.advect_gauge ? adv(dal) : R(0)) + ko
                        - muL * Khat;
-            if constexpr (RK) {
-                const double v = combine(ALPHA, ka, staged(), o);
-                at(ob + ALPHA * fs, upt8) = v > a.alpha_floor ? v : a.alpha_floor;
-            } else {
-                at(ob + ALPHA * fs, upt8) = double(ka);
-            }
+            nal = combine(ka, staged(), o);
+            if constexpr (RK)
+                nal.w = nal.w > a.alpha_floor ? nal.w : a.alpha_floor;
         }
+        ft.arrive();
+        if (active)
+            write(ALPHA, nal);
 
         // ---- chi: R^chi_ij, D_i D_j alpha; chi is complete, and with it the
         // sources of Khat, Theta and At
@@ -448,12 +470,10 @@ stage_kernel(const StageArgs a)
             derivs2(dchi, dd, ko);
             const R kc = adv(dchi) + ko
                        + R(2.0 / 3.0) * chi * (alpha * K - divb);
-            if constexpr (RK) {
-                const double v = combine(CHI, kc, staged(), o);
-                at(ob + CHI * fs, upt8) = v > a.chi_floor ? v : a.chi_floor;
-            } else {
-                at(ob + CHI * fs, upt8) = double(kc);
-            }
+            New nchi = combine(kc, staged(), o);
+            if constexpr (RK)
+                nchi.w = nchi.w > a.chi_floor ? nchi.w : a.chi_floor;
+            write(CHI, nchi);   // here: held to the end of this stage they spill
             {
                 R dchi2 = R(0), ca = R(0);   // gt^{kl} d_k chi d_l (chi, alpha)
                 sfor<3>([&](auto P0_c) __attribute__((always_inline)) {
@@ -599,6 +619,7 @@ stage_kernel(const StageArgs a)
         sfor<2>([&](auto Q_c) __attribute__((always_inline)) {
             constexpr int q = decltype(Q_c)::value;
             stage(std::integral_constant<int, q == 0 ? KHAT : THETA>{});
+            New nw;
             if (active) {
                 const Old o = old(q == 0 ? KHAT : THETA);
                 if constexpr (q == 1 && RK) {
@@ -622,14 +643,17 @@ stage_kernel(const StageArgs a)
                     });
                 }
                 const R kq = adv(d) + ko + (q == 0 ? Kpart : Tpart);
-                finish(q == 0 ? KHAT : THETA, kq, staged(), o);
+                nw = combine(kq, staged(), o);
             }
+            ft.arrive();
+            if (active)
+                write(q == 0 ? KHAT : THETA, nw);
         });
         // Gamma-tilde is complete
         if (active) {
             sfor<3>([&](auto I_c) __attribute__((always_inline)) {
                 constexpr int ii = decltype(I_c)::value;
-                finish(GAMX + ii, rG[ii], gam0[ii], gamo[ii]);
+                write(GAMX + ii, combine(rG[ii], gam0[ii], gamo[ii]));
             });
         }
 
@@ -638,6 +662,7 @@ stage_kernel(const StageArgs a)
         sfor<6>([&](auto Q_c) __attribute__((always_inline)) {
             constexpr int q = decltype(Q_c)::value;
             stage(std::integral_constant<int, AXX + q>{});
+            New nw;
             if (active) {
                 const Old o = old(AXX + q);
                 if constexpr (q == 5 && RK) {
@@ -658,10 +683,16 @@ stage_kernel(const StageArgs a)
                         Mc[jj] += gi[S(ii, 0)] * d[0] + gi[S(ii, 1)] * d[1] + gi[S(ii, 2)] * d[2];
                 }
                 const R kA = adv(d) + ko + get(18 + q);
-                if constexpr (RK)
-                    vA[q] = combine(AXX + q, kA, staged(), o);
-                else
-                    at(ob + (AXX + q) * fs, upt8) = double(kA);
+                nw = combine(kA, staged(), o);
+            }
+            ft.arrive();
+            if (active) {
+                if constexpr (RK) {
+                    vA[q] = nw.w;
+                    write1(AXX + q, nw);
+                } else {
+                    write(AXX + q, nw);
+                }
             }
         });
         if constexpr (RK) {

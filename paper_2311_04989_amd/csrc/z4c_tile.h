@@ -507,6 +507,15 @@ struct FieldTile {
         zo = t;
         asm volatile("" : "+v"(po), "+v"(zo));
     }
+    // Waits for the requested field's points.  Called by every lane before the
+    // results of the staged field are stored: loads and stores are counted
+    // together, so the wait at the next staging would be for those stores too.
+    __device__ __forceinline__ void arrive()
+    {
+#pragma unroll
+        for (int q = 0; q < D::LZ; ++q)
+            asm volatile("" ::"v"(st.pf[q]));
+    }
     // lowest taps of this thread's stencils, centre at RAD strides
     __device__ __forceinline__ const double *xtaps() const { return pl + po + D::RAD * D::PX; }
     __device__ __forceinline__ const double *ytaps() const { return pl + po + D::RAD; }
