@@ -407,10 +407,19 @@ z4c_status build_tiles(z4c_plan *P)
     for (const SizeClass &c : P->classes)
         for (int b : c.blocks) {
             tstart[b] = (long long)tiles.size();
-            for (int k0 = 0; k0 < c.nz; k0 += TILE_Z)
-                for (int j0 = 0; j0 < c.ny; j0 += TILE_Y)
-                    for (int i0 = 0; i0 < c.nx; i0 += TILE_X)
-                        tiles.push_back(Tile{b, i0, j0, k0});
+            // Slabs of whole x rows, as many as an XCD has tiles in flight (32
+            // CUs at two workgroups), swept through z: a tile's z neighbours
+            // are staged while its halo points are still in the XCD's L2, and
+            // the 64-byte row pieces of x neighbours are written together.
+            // 8 x 128^3 star step: whole z layers (256 tiles) 30.8 ms, slabs
+            // of 4 rows 28.9, of 8 rows 30.1; bricks of 4 x 4 x 4 tiles 33.8.
+            // Blocks up to 64 points wide and deep are one slab.
+            const int row = (c.nx + TILE_X - 1) / TILE_X, rows = (64 + row - 1) / row;
+            for (int j1 = 0; j1 < c.ny; j1 += rows * TILE_Y)
+                for (int k0 = 0; k0 < c.nz; k0 += TILE_Z)
+                    for (int j0 = j1; j0 < c.ny && j0 < j1 + rows * TILE_Y; j0 += TILE_Y)
+                        for (int i0 = 0; i0 < c.nx; i0 += TILE_X)
+                            tiles.push_back(Tile{b, i0, j0, k0});
             tcount[b] = (int)((long long)tiles.size() - tstart[b]);
         }
     if (tiles.size() > (size_t)INT_MAX)

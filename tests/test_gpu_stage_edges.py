@@ -95,3 +95,29 @@ def test_tile_edges(order, n, rule):
     rows = compare(bt, got["stored"][3], O.constraints(bt)[0], c80, nfields=W.NC)
     assert_parity(rows, f"tile edges {order} {n} {rule} constraints\n" + report(rows))
     np.testing.assert_allclose(got["stored"][4].reshape(-1, 8, 2), n80, rtol=1e-10, atol=1e-300)
+
+
+# Tile rows along x of over 8 tiles: slabs of 4 rows (17 tiles) and of one (66)
+@pytest.mark.parametrize("n", [(130, 43, 5), (521, 9, 5)])
+def test_tile_slabs(n):
+    from paper_2311_04989_amd import z4c as Z
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    O.build(force=False)
+    print(f"tile slabs: {n}", flush=True)
+    bt = _blocks(6, n, matter=False)
+    plan = Z.plan_for(bt)
+    u = torch.from_numpy(bt.u).to("cuda:0")
+    rhs = torch.full_like(u, np.nan)
+    cons = torch.zeros(bt.total_c, dtype=torch.float64, device="cuda:0")
+    norms = torch.zeros(16 * len(bt.blocks), dtype=torch.float64, device="cuda:0")
+    plan.rhs(u, None, rhs)
+    plan.constraints(u, None, cons, norms)
+    torch.cuda.synchronize()
+    plan.close()
+    rows = compare(bt, rhs.cpu().numpy(), O.rhs(bt), O.rhs(bt, ext=True))
+    assert_parity(rows, f"tile slabs {n}\n" + report(rows))
+    c80, n80 = O.constraints(bt, ext=True)
+    rows = compare(bt, cons.cpu().numpy(), O.constraints(bt)[0], c80, nfields=W.NC)
+    assert_parity(rows, f"tile slabs {n} constraints\n" + report(rows))
+    np.testing.assert_allclose(norms.cpu().numpy().reshape(-1, 8, 2), n80, rtol=1e-10, atol=1e-300)
