@@ -20,6 +20,15 @@ enum MatterField : int { M_RHO = 0, M_SX, M_SY, M_SZ, M_SXX, M_SXY, M_SXZ, M_SYY
                          NMATTER = 10 };
 enum ConsField : int { C_H = 0, C_MX, C_MY, C_MZ, C_THETA, C_ZX, C_ZY, C_ZZ, NCONS = 8 };
 
+// Logical workgroup index: consecutive logical indices on the same XCD
+// (the dispatcher places workgroup w on XCD w % 8).
+__device__ __forceinline__ int xcd_logical(int w, int G)
+{
+    const int q = G >> 3, r = G & 7;
+    const int x = w & 7, k = w >> 3;
+    return x * q + (x < r ? x : r) + k;
+}
+
 // What a tile kernel produces.
 enum Mode : int { MODE_RHS = 0, MODE_RK = 1, MODE_CONS = 2, MODE_RK_MON = 3 };
 

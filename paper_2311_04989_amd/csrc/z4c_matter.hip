@@ -26,8 +26,8 @@ struct z4c_mplan {
     std::vector<z4c_mblock> blocks;
     bool device = false;
     z4c_mblock *blocks_d = nullptr;
-    void *cc_tiles_d = nullptr;   // MTile[n_cc]: interpolation columns over every stored cell
-    void *vc_tiles_d = nullptr;   // MTile[n_vc]: interpolation columns over vertices [0, nc]
+    void *cc_tiles_d = nullptr;   // ITile[n_cc]: interpolation columns over every stored cell
+    void *vc_tiles_d = nullptr;   // ITile[n_vc]: interpolation columns over vertices [0, nc]
     void *pt_tiles_d = nullptr;   // MTile[n_pt]: point tiles over every stored cell
     int n_cc = 0, n_vc = 0, n_pt = 0;
 };
@@ -35,18 +35,23 @@ struct z4c_mplan {
 namespace z4c {
 namespace {
 
-// interpolation columns: ITX x ITY outputs per plane, ITZ planes, one thread per (x, y)
-// (32 x 8 x 16 and four planes in flight measured best on the 8 x 128^3-cell
-// level set among 16 x 16, 32 x 16 and 32 x 8 columns of 16 or 32 planes and
-// one to six planes in flight)
-constexpr int ITX = 32, ITY = 8, ITZ = 16, INT_ = ITX * ITY;
-constexpr int PD = 4;   // input planes in flight per workgroup
+constexpr int INT_ = 256;   // threads of an interpolation workgroup
 // ADM projections: chunks of PNT consecutive stored cells, one per thread
 constexpr int PNT = 512;
 
 struct MTile {
-    int block, i0, j0, k0;   // tile origin (stored CC index, or vertex index)
+    int block, i0;   // chunk of stored cells from linear index i0
 };
+
+// Column of an interpolation: outputs [i0, i0 + w) x [j0, j0 + h) x
+// [k0, k0 + d) of the call's range, one thread per (x, y).
+struct ITile {
+    int block, i0, j0, k0, w, h, d;
+};
+
+// Buffer size and the byte offset of outputs that are not stored; a column's
+// rows span less.
+constexpr unsigned OUTSIDE = 0xfffffff0u;
 
 // Weight k of the Lagrange polynomial through O equally spaced nodes,
 // evaluated midway between the two central nodes.
@@ -71,114 +76,139 @@ __device__ __forceinline__ double midsum(const double *c, int st)
     return s;
 }
 
-// TO_CC: the 7 conformal-geometry fields of the VC state to cells (stored CC
+// Interpolates fields [f0, f0 + nf) of one column, f0 = (logical workgroup / n)
+// nf: TO_CC the 7 conformal-geometry fields of the VC state to cells (stored CC
 // index in [ngc - ext, ngc + nc + ext)); otherwise the 10 ADM fields from the
 // CC sources to vertices [0, nc].
+// Each input plane goes through LDS and its x sums through LDS again; the last
+// O y sums of a column stay in registers.  Both LDS arrays are double-buffered,
+// so that the x sums of a plane and the y and z sums of the one before it share
+// one barrier interval.  Loads and stores take no branch (positions outside are
+// clamped into the stored array and feed no output of the range; stores outside
+// it fall to the buffer's bounds check): the wait for a plane then counts what
+// was issued after it and leaves the younger planes in flight.
+// What bounds it: HBM, at 3.7 to 4.3 TB/s of reads and writes, every point once
+// (1.51 + 1.40 GB for the 10 fields of 8 x 128^3 cells at order 6).  Against
+// 32 x 8 x 16 columns with two barriers per plane and the fields in a loop:
+// 1090 -> 783 us, the 7 metric fields at order 4 674 -> 557 us, and 8 x 20^3
+// cells 81 -> 10 and 47 -> 9 us.  Four waves per SIMD (all that fit: 902 and 674
+// us where four took 856 and 660).  The fields of a column one after the other
+// in one workgroup 1016 us, side by side on one XCD 1047 us.
 template <int O, bool TO_CC>
 __global__ void __launch_bounds__(INT_)
-interp_kernel(const z4c_mblock *blocks, const MTile *tiles, int ext, const double *in, double *out)
+    __attribute__((amdgpu_waves_per_eu(4, 4)))
+interp_kernel(const z4c_mblock *blocks, const ITile *tiles, int n, int nf, int ext,
+              const double *in, double *out)
 {
-    constexpr int LX = ITX + O - 1, LY = ITY + O - 1;
-    constexpr int NPL = LX * LY;                      // one input plane
-    constexpr int NLD = (NPL + INT_ - 1) / INT_;      // its values per thread
-    constexpr int NP = ITZ + O - 1;                   // input planes per column
-    __shared__ double s_pl[NPL];
-    __shared__ double s_x[ITX * LY];
-    const MTile T = tiles[blockIdx.x];
+    constexpr int PD = O == 6 ? 6 : 4;   // planes in flight; a multiple of O and of 2
+    constexpr int NLD = 2;               // values of an input plane per thread
+    __shared__ __attribute__((aligned(16))) double s_pl[2][NLD * INT_ + 4];
+    __shared__ __attribute__((aligned(16))) double s_x[2][2 * INT_];
+    const int wg = xcd_logical(blockIdx.x, gridDim.x);
+    const ITile T = tiles[wg % n];
     const z4c_mblock B = blocks[T.block];
-    const int n[3] = {B.ncx, B.ncy, B.ncz};
-    const int o[3] = {T.i0, T.j0, T.k0};
-    constexpr int TD[3] = {ITX, ITY, ITZ};
-    // per direction: the first valid tile-local output index and one past
-    // the last, and the stored input index of the first stencil point of
-    // tile-local output 0
-    int lo[3], hi[3], in0[3];
+    const int nc[3] = {B.ncx, B.ncy, B.ncz}, o[3] = {T.i0, T.j0, T.k0};
+    // per direction: outputs left in the range, stored index of output 0 and
+    // of its first input, stored extents
+    int left[3], out0[3], in0[3], is[3], os[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        if constexpr (TO_CC) {
-            lo[d] = B.ngc - ext - o[d];
-            hi[d] = B.ngc + n[d] + ext - o[d];
-            in0[d] = o[d] - B.ngc - O / 2 + 1 + B.ngv;
-        } else {
-            lo[d] = -o[d];
-            hi[d] = n[d] + 1 - o[d];
-            in0[d] = o[d] - O / 2 + B.ngc;
-        }
+        const int vc = nc[d] + 1 + 2 * B.ngv, cc = nc[d] + 2 * B.ngc;
+        left[d] = (TO_CC ? nc[d] + 2 * ext : nc[d] + 1) - o[d];
+        out0[d] = o[d] + (TO_CC ? B.ngc - ext : B.ngv);
+        in0[d] = o[d] - O / 2 + (TO_CC ? B.ngv + 1 - ext : B.ngc);
+        is[d] = TO_CC ? vc : cc;
+        os[d] = TO_CC ? cc : vc;
     }
-    if (hi[0] <= 0 || hi[1] <= 0 || hi[2] <= 0 || lo[0] >= TD[0] || lo[1] >= TD[1]
-        || lo[2] >= TD[2])
-        return;   // the whole column lies outside this call's range (uniform)
-    const int isx = TO_CC ? B.ncx + 1 + 2 * B.ngv : B.ncx + 2 * B.ngc;
-    const int isy = TO_CC ? B.ncy + 1 + 2 * B.ngv : B.ncy + 2 * B.ngc;
-    const int isz = TO_CC ? B.ncz + 1 + 2 * B.ngv : B.ncz + 2 * B.ngc;
-    const int osx = TO_CC ? B.ncx + 2 * B.ngc : B.ncx + 1 + 2 * B.ngv;
-    const int osy = TO_CC ? B.ncy + 2 * B.ngc : B.ncy + 1 + 2 * B.ngv;
-    const long long ibase = TO_CC ? B.vs_offset : B.ca_offset;
-    const long long ifs = TO_CC ? B.vc_stride : B.cc_stride;
-    const long long obase = TO_CC ? B.cg_offset : B.vm_offset;
-    const long long ofs = TO_CC ? B.cc_stride : B.vc_stride;
-    const int og = TO_CC ? 0 : B.ngv;   // stored output index = tile origin + local + og
-    const int t = threadIdx.x, tx = t % ITX, ty = t / ITX;
-    const bool col_ok = tx >= lo[0] && tx < hi[0] && ty >= lo[1] && ty < hi[1];
-    // plane element q of this thread: input offset within a plane (positions
-    // outside the stored array are clamped into it; they feed only outputs
-    // outside the call's range)
-    long long eoff[NLD];
+    if (left[0] <= 0 || left[1] <= 0 || left[2] <= 0)
+        return;   // outside this call's range (uniform)
+    const int nz = T.d < left[2] ? T.d : left[2];
+    const unsigned t = threadIdx.x;
+    // input plane: this thread's values, their offsets and LDS places (rows
+    // padded to an even length)
+    const unsigned lx = T.w + O - 1, ly = T.h + O - 1, lxp = (lx + 1) & ~1u;
+    long long ioff[NLD];
+    unsigned place[NLD];
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
-        const int e = t + q * INT_;
-        const int lx = e % LX, ly = e / LX;
-        const int gx = min(max(in0[0] + lx, 0), isx - 1);
-        const int gy = min(max(in0[1] + ly, 0), isy - 1);
-        eoff[q] = gx + (long long)isx * gy;
+        const unsigned e = t + q * INT_, y = e / lx, x = e - y * lx;
+        const int gx = min(max(in0[0] + (int)x, 0), is[0] - 1);
+        const int gy = min(max(in0[1] + (int)y, 0), is[1] - 1);
+        ioff[q] = gx + (long long)is[0] * gy;
+        place[q] = y < ly ? y * lxp + x : NLD * INT_ + 2;
     }
-    const long long pstride = (long long)isx * isy;
-    constexpr int NF = TO_CC ? 7 : 10;
-    for (int f = 0; f < NF; ++f) {
-        const double *src = in + ibase + f * ifs;
-        double *dst = out + obase + f * ofs;
-        double r[PD][NLD];   // planes p .. p + PD - 1 in flight
-        auto load = [&](int p) __attribute__((always_inline)) {
-            const long long zo = min(max(in0[2] + p, 0), isz - 1) * pstride;
+    // x sums of two neighbouring outputs of row xr
+    const unsigned pw = (T.w + 1) / 2, xr = t / pw, xp = t - xr * pw;
+    const bool xsum = xr < ly;
+    const unsigned xsrc = xr * lxp + 2 * xp, xdst = 2 * t;
+    // this thread's column; past the buffer's end where it has no output
+    const unsigned ty = t / T.w, tx = t - ty * T.w;
+    const unsigned ysrc = (ty < (unsigned)T.h ? ty : T.h - 1) * 2 * pw + tx;
+    const bool ok = ty < (unsigned)T.h && (int)tx < left[0] && (int)ty < left[1];
+    const unsigned ooff = ok ? 8u * (tx + (unsigned)os[0] * ty) : OUTSIDE;
+    const long long ips = (long long)is[0] * is[1], ops = (long long)os[0] * os[1];
+    const int np = nz + O - 1;   // input planes of the column
+
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const int fe = TO_CC ? 7 : 10, f0 = wg / n * nf, f1 = f0 + nf < fe ? f0 + nf : fe;
+    for (int f = f0; f < f1; ++f) {
+        const double *src = in + (TO_CC ? B.vs_offset + f * B.vc_stride
+                                        : B.ca_offset + f * B.cc_stride);
+        double *dst = out + (TO_CC ? B.cg_offset + f * B.cc_stride : B.vm_offset + f * B.vc_stride)
+                    + out0[0] + (long long)os[0] * out0[1] + out0[2] * ops;
+        double r[PD][NLD];   // planes p .. p + PD - 1
+        auto load = [&](int j, int p) __attribute__((always_inline)) {
+            const int z = min(max(in0[2] + min(p, np - 1), 0), is[2] - 1);
+            const double *c = src + z * ips;
 #pragma unroll
             for (int q = 0; q < NLD; ++q)
-                if ((q + 1) * INT_ <= NPL || t + q * INT_ < NPL)
-                    r[p % PD][q] = src[zo + eoff[q]];
+                r[j][q] = c[ioff[q]];
         };
 #pragma unroll
         for (int p = 0; p < PD; ++p)
-            load(p);
-        double col[O];   // y-reduced values of the last O input planes
+            load(p, p);
+        double col[O];   // y sums of the last O planes, plane p in col[p % O]
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int k = 0; k < O; ++k)
+            col[k] = 0.0;
+        for (int p0 = 0;; p0 += PD) {
 #pragma unroll
-            for (int q = 0; q < NLD; ++q)
-                if ((q + 1) * INT_ <= NPL || t + q * INT_ < NPL)
-                    s_pl[t + q * INT_] = r[p % PD][q];
-            if (p + PD < NP)
-                load(p + PD);
-            __syncthreads();
-            for (int e = t; e < ITX * LY; e += INT_) {
-                const int x = e % ITX, ly = e / ITX;
-                s_x[e] = midsum<O>(s_pl + ly * LX + x, 1);
-            }
-            __syncthreads();
+            for (int j = 0; j < PD; ++j) {
+                const int p = p0 + j;
+                if (p > np)
+                    goto done;
 #pragma unroll
-            for (int k = 0; k + 1 < O; ++k)
-                col[k] = col[k + 1];
-            col[O - 1] = midsum<O>(s_x + ty * ITX + tx, ITX);
-            if (p >= O - 1) {
-                const int z = p - (O - 1);
-                if (col_ok && z >= lo[2] && z < hi[2]) {
-                    double v = 0.0;
+                for (int q = 0; q < NLD; ++q)
+                    s_pl[j & 1][place[q]] = r[j][q];
+                load(j, p + PD);
+                __syncthreads();
+                if (xsum) {
+                    const double2 *c = (const double2 *)(s_pl[j & 1] + xsrc);
+                    double v[O + 2];
 #pragma unroll
-                    for (int k = 0; k < O; ++k)
-                        v += midw<O>(k) * col[k];
-                    dst[(o[0] + og + tx) + (long long)osx * ((o[1] + og + ty)
-                        + (long long)osy * (o[2] + og + z))] = v;
+                    for (int k = 0; k < O + 2; k += 2) {
+                        const double2 w = c[k / 2];
+                        v[k] = w.x;
+                        v[k + 1] = w.y;
+                    }
+                    *(double2 *)(s_x[j & 1] + xdst) =
+                        make_double2(midsum<O>(v, 1), midsum<O>(v + 1, 1));
                 }
+                // plane p - 1; output plane p - O, below the range at first
+                constexpr int M = PD - 1;
+                col[(j + M) % O] = midsum<O>(s_x[(j + 1) & 1] + ysrc, 2 * pw);
+                double v = 0.0;
+#pragma unroll
+                for (int k = 0; k < O; ++k)
+                    v += midw<O>(k) * col[(j + M + 1 + k) % O];
+                const auto plane = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)(dst + (p - O) * ops), 0, p >= O ? (int)OUTSIDE : 0, 0x00027000);
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), plane, ooff, 0,
+                                                      0);
             }
         }
+    done:
+        __syncthreads();   // the LDS arrays are written again by the next field
     }
 }
 
@@ -650,20 +680,68 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
         a.status[B.cf_offset + p] = st;
 }
 
+int share(int n, int most)
+{
+    const int parts = (n + most - 1) / most;
+    return (n + parts - 1) / parts;
+}
+
+// Extents w x h of the columns over nx x ny outputs (rows stored `row` apart):
+// the widest a workgroup can hold, unless a narrower one needs a quarter fewer
+// (wide pieces of rows: the 7 metric fields of 8 x 128^3 cells 565 us, with the
+// fewest columns 660; short of 129 points the fewest are often the widest).
+// The even share of the outputs, not full columns and a remainder.
+void column_shape(int nx, int ny, int row, int &w, int &h)
+{
+    long long best = INT64_MAX;
+    w = h = 1;
+    for (int a = std::min(nx, 64); a >= 1; --a) {
+        // a thread per output, two per point of an input plane (rows of even
+        // length) and one per pair of x sums, at order 6; offsets below OUTSIDE
+        const int b = std::min({ny, INT_ / a, 2 * INT_ / ((a + 6) & ~1) - 5,
+                                INT_ / ((a + 1) / 2) - 5,
+                                std::max(1, (int)((OUTSIDE / 8 - 64) / row))});
+        if (b < 1)
+            continue;
+        const long long c = ((nx + a - 1LL) / a) * ((ny + b - 1LL) / b);
+        if (best == INT64_MAX || 4 * c < 3 * best) {
+            best = c;
+            w = a;
+            h = b;
+        }
+    }
+    w = share(nx, w);
+    h = share(ny, h);
+}
+
+// Cuts nx x ny x nz outputs of a block into columns of up to `most` planes.
+void cut_columns(int block, int nx, int ny, int nz, int row, int most, std::vector<ITile> &out)
+{
+    int w, h;
+    column_shape(nx, ny, row, w, h);
+    const int d = share(nz, most);
+    for (int k = 0; k < nz; k += d)
+        for (int j = 0; j < ny; j += h)
+            for (int i = 0; i < nx; i += w)
+                out.push_back({block, i, j, k, w, h, d});
+}
+
 template <bool TO_CC>
 hipError_t launch_interp(int order, const z4c_mplan *P, int ext, const double *in, double *out,
                          hipStream_t s)
 {
-    const MTile *tiles = (const MTile *)(TO_CC ? P->cc_tiles_d : P->vc_tiles_d);
-    const int n = TO_CC ? P->n_cc : P->n_vc;
+    const ITile *tiles = (const ITile *)(TO_CC ? P->cc_tiles_d : P->vc_tiles_d);
+    const int n = TO_CC ? P->n_cc : P->n_vc, fields = TO_CC ? 7 : 10;
     if (n == 0)
         return hipSuccess;
+    // a workgroup per column and field, where a grid can hold them
+    const int nf = n <= INT32_MAX / fields ? 1 : fields, grid = nf == 1 ? n * fields : n;
     if (order == 2)
-        interp_kernel<2, TO_CC><<<n, INT_, 0, s>>>(P->blocks_d, tiles, ext, in, out);
+        interp_kernel<2, TO_CC><<<grid, INT_, 0, s>>>(P->blocks_d, tiles, n, nf, ext, in, out);
     else if (order == 4)
-        interp_kernel<4, TO_CC><<<n, INT_, 0, s>>>(P->blocks_d, tiles, ext, in, out);
+        interp_kernel<4, TO_CC><<<grid, INT_, 0, s>>>(P->blocks_d, tiles, n, nf, ext, in, out);
     else
-        interp_kernel<6, TO_CC><<<n, INT_, 0, s>>>(P->blocks_d, tiles, ext, in, out);
+        interp_kernel<6, TO_CC><<<grid, INT_, 0, s>>>(P->blocks_d, tiles, n, nf, ext, in, out);
     return hipGetLastError();
 }
 
@@ -701,7 +779,9 @@ z4c_status z4c_mplan_create(const z4c_mblock *blocks, int nblocks, int flags, z4
         return set_error(Z4C_EINVAL, "blocks is NULL or nblocks < 1");
     if (flags & ~Z4C_PLAN_NO_DEVICE)
         return set_error(Z4C_EINVAL, "unknown flags");
-    std::vector<MTile> cc, vc, pt;
+    std::vector<ITile> cc, vc;
+    std::vector<MTile> pt;
+    long long columns = 0;
     for (int b = 0; b < nblocks; ++b) {
         const z4c_mblock &B = blocks[b];
         char buf[160];
@@ -724,21 +804,27 @@ z4c_status z4c_mplan_create(const z4c_mblock *blocks, int nblocks, int flags, z4
             return set_error(Z4C_EINVAL, buf);
         }
         const int sc[3] = {B.ncx + 2 * B.ngc, B.ncy + 2 * B.ngc, B.ncz + 2 * B.ngc};
-        for (int k = 0; k < sc[2]; k += ITZ)
-            for (int j = 0; j < sc[1]; j += ITY)
-                for (int i = 0; i < sc[0]; i += ITX)
-                    cc.push_back({b, i, j, k});
-        for (int k = 0; k <= B.ncz; k += ITZ)
-            for (int j = 0; j <= B.ncy; j += ITY)
-                for (int i = 0; i <= B.ncx; i += ITX)
-                    vc.push_back({b, i, j, k});
         const long long ncs = (long long)sc[0] * sc[1] * sc[2];
         if (ncs > INT32_MAX) {
             snprintf(buf, sizeof buf, "block %d: more than 2^31 stored cells", b);
             return set_error(Z4C_EINVAL, buf);
         }
         for (long long c = 0; c < ncs; c += PNT)
-            pt.push_back({b, (int)c, 0, 0});
+            pt.push_back({b, (int)c});
+        int w, h;
+        column_shape(sc[0], sc[1], sc[0], w, h);
+        columns += ((sc[0] + w - 1LL) / w) * ((sc[1] + h - 1LL) / h);
+    }
+    // Planes of a column: long ones read fewer planes twice, few blocks need
+    // short ones to occupy the chip (10 fields, at most 17 / 33 / 65 planes: 1 x
+    // 64^3 cells, 22 columns, 16 / 18 / 24 us; 2 x 64^3 26 / 23 / 29 us; 1 x
+    // 128^3, 80 columns, 119 / 109 / 106 us; 8 x 128^3 887 / 807 / 783 us).
+    const int most = (int)std::min(std::max(columns, 17LL), 65LL);
+    for (int b = 0; b < nblocks; ++b) {
+        const z4c_mblock &B = blocks[b];
+        const int gc = 2 * B.ngc;
+        cut_columns(b, B.ncx + gc, B.ncy + gc, B.ncz + gc, B.ncx + gc, most, cc);
+        cut_columns(b, B.ncx + 1, B.ncy + 1, B.ncz + 1, B.ncx + 1 + 2 * B.ngv, most, vc);
     }
     if (cc.size() > (size_t)INT32_MAX || vc.size() > (size_t)INT32_MAX
         || pt.size() > (size_t)INT32_MAX)
@@ -751,19 +837,19 @@ z4c_status z4c_mplan_create(const z4c_mblock *blocks, int nblocks, int flags, z4
     if (!(flags & Z4C_PLAN_NO_DEVICE)) {
         hipError_t e = hipMalloc(&P->blocks_d, sizeof(z4c_mblock) * nblocks);
         if (e == hipSuccess)
-            e = hipMalloc(&P->cc_tiles_d, sizeof(MTile) * cc.size());
+            e = hipMalloc(&P->cc_tiles_d, sizeof(ITile) * cc.size());
         if (e == hipSuccess)
-            e = hipMalloc(&P->vc_tiles_d, sizeof(MTile) * vc.size());
+            e = hipMalloc(&P->vc_tiles_d, sizeof(ITile) * vc.size());
         if (e == hipSuccess)
             e = hipMalloc(&P->pt_tiles_d, sizeof(MTile) * pt.size());
         if (e == hipSuccess)
             e = hipMemcpy(P->blocks_d, blocks, sizeof(z4c_mblock) * nblocks,
                           hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy(P->cc_tiles_d, cc.data(), sizeof(MTile) * cc.size(),
+            e = hipMemcpy(P->cc_tiles_d, cc.data(), sizeof(ITile) * cc.size(),
                           hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy(P->vc_tiles_d, vc.data(), sizeof(MTile) * vc.size(),
+            e = hipMemcpy(P->vc_tiles_d, vc.data(), sizeof(ITile) * vc.size(),
                           hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy(P->pt_tiles_d, pt.data(), sizeof(MTile) * pt.size(),

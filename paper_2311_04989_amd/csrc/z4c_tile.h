@@ -130,15 +130,6 @@ __device__ __forceinline__ R symtrace(const R gi[6], const R t[6])
            + R(2) * (gi[1] * t[1] + gi[2] * t[2] + gi[4] * t[4]);
 }
 
-// Logical workgroup index: consecutive logical indices on the same XCD
-// (the dispatcher places workgroup w on XCD w % 8).
-__device__ __forceinline__ int xcd_logical(int w, int G)
-{
-    const int q = G >> 3, r = G & 7;
-    const int x = w & 7, k = w >> 3;
-    return x * q + (x < r ? x : r) + k;
-}
-
 // Tile of this workgroup: one workgroup per tile, workgroup w taking the tile
 // of logical index xcd_logical(w), so that consecutive tiles (neighbours in
 // one block, which share halo points) run on one XCD and meet in its L2.
