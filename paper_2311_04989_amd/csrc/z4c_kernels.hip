@@ -12,11 +12,17 @@ namespace z4c {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Ghost refresh: one thread per ghost point, all 22 fields
+// Ghost refresh: one thread per ghost point, all 22 fields, every load issued
+// before the first store.  What bounds it: memory on large sets, where the
+// pieces of 4 points at the ends of rows are parts of sectors that it reads,
+// merges and writes back; latency on small ones.  Against a loop that waited
+// for each field, 64-bit divisions and one slab per end: 512 blocks of 16^3
+// 502 -> 424 us, 8 x 128^3 452 -> 406 us (436 with neighbouring workgroups on
+// different XCDs), one of 16^3 8.8 -> 3.9 us.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) ghost_kernel(const GhostArgs g, long long total)
 {
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long gid = (long long)xcd_logical(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
     if (gid >= total)
         return;
     // block by binary search over the prefix sums
@@ -30,41 +36,35 @@ __global__ void __launch_bounds__(256) ghost_kernel(const GhostArgs g, long long
     }
     const int b = lo;
     const z4c_block B = g.blocks[b];
-    long long r = gid - g.ghost_start[b];
+    // 32 bits hold the ghost points of a block (22 fields each, in memory)
+    unsigned r = (unsigned)(gid - g.ghost_start[b]);
     const int ng = B.ng;
-    const int ex = B.nx + 2 * ng, ey = B.ny + 2 * ng, ez = B.nz + 2 * ng;
+    const unsigned ex = B.nx + 2 * ng, ey = B.ny + 2 * ng;
     int i, j, k;
-    // z slabs (full planes), then y slabs (interior z), then x slabs
-    const long long zslab = (long long)ng * ey * ex;
-    const long long yslab = (long long)ng * B.nz * ex;
+    // z slabs (full planes), then y slabs (interior z), then the ends of the rows
+    const unsigned zslab = ng * ey * ex, yslab = ng * B.nz * ex;
     if (r < 2 * zslab) {
         const int side = r >= zslab;
         r -= side * zslab;
-        const int kk = (int)(r / ((long long)ey * ex));
-        const int rem = (int)(r % ((long long)ey * ex));
-        k = side ? B.nz + kk : kk - ng;
-        j = rem / ex - ng;
-        i = rem % ex - ng;
+        const unsigned row = r / ex, kk = row / ey;
+        k = side ? B.nz + (int)kk : (int)kk - ng;
+        j = (int)(row - kk * ey) - ng;
+        i = (int)(r - row * ex) - ng;
     } else if ((r -= 2 * zslab) < 2 * yslab) {
         const int side = r >= yslab;
         r -= side * yslab;
-        const int kk = (int)(r / ((long long)ng * ex));
-        const int rem = (int)(r % ((long long)ng * ex));
-        k = kk;
-        const int jj = rem / ex;
-        j = side ? B.ny + jj : jj - ng;
-        i = rem % ex - ng;
+        const unsigned row = r / ex, kk = row / ng, jj = row - kk * ng;
+        k = (int)kk;
+        j = side ? B.ny + (int)jj : (int)jj - ng;
+        i = (int)(r - row * ex) - ng;
     } else {
+        // both ends of a row: the upper one and the next row's lower one are
+        // neighbours in memory
         r -= 2 * yslab;
-        const long long xslab = (long long)ng * B.nz * B.ny;
-        const int side = r >= xslab;
-        r -= side * xslab;
-        const int kk = (int)(r / ((long long)B.ny * ng));
-        const int rem = (int)(r % ((long long)B.ny * ng));
-        k = kk;
-        j = rem / ng;
-        const int ii = rem % ng;
-        i = side ? B.nx + ii : ii - ng;
+        const unsigned row = r / (2 * ng), ii = r - row * 2 * ng;
+        k = (int)(row / B.ny);
+        j = (int)(row - k * B.ny);
+        i = ii < (unsigned)ng ? (int)ii - ng : B.nx + (int)ii - ng;
     }
     const int ox = i < 0 ? -1 : (i >= B.nx ? 1 : 0);
     const int oy = j < 0 ? -1 : (j >= B.ny ? 1 : 0);
@@ -75,23 +75,28 @@ __global__ void __launch_bounds__(256) ghost_kernel(const GhostArgs g, long long
         src_b = b;
     else if (g.policy == Z4C_GHOST_NEIGHBOUR)
         src_b = g.neighbours[b * 27 + (oz + 1) * 9 + (oy + 1) * 3 + (ox + 1)];
-    double *ub = g.u + B.offset;
+    const double *src;
+    long long sfs = B.field_stride;
     if (src_b < 0) {
-        if (g.frozen) {
-            const double *fb = g.frozen + B.offset;
-            for (int f = 0; f < NFIELD; ++f)
-                ub[f * B.field_stride + dst] = fb[f * B.field_stride + dst];
-        }
-        return;
+        if (!g.frozen)
+            return;
+        src = g.frozen + B.offset + dst;
+    } else {
+        const z4c_block Sb = g.blocks[src_b];
+        const int si = i - ox * B.nx, sj = j - oy * B.ny, sk = k - oz * B.nz;
+        const int sex = Sb.nx + 2 * Sb.ng, sey = Sb.ny + 2 * Sb.ng;
+        src = g.u + Sb.offset + (long long)(sk + Sb.ng) * sey * sex
+            + (long long)(sj + Sb.ng) * sex + (si + Sb.ng);
+        sfs = Sb.field_stride;
     }
-    const z4c_block Sb = g.blocks[src_b];
-    const int si = i - ox * B.nx, sj = j - oy * B.ny, sk = k - oz * B.nz;
-    const int sex = Sb.nx + 2 * Sb.ng, sey = Sb.ny + 2 * Sb.ng;
-    const long long src = (long long)(sk + Sb.ng) * sey * sex + (long long)(sj + Sb.ng) * sex
-                        + (si + Sb.ng);
-    const double *sbp = g.u + Sb.offset;
+    double *out = g.u + B.offset + dst;
+    double v[NFIELD];
+#pragma unroll
     for (int f = 0; f < NFIELD; ++f)
-        ub[f * B.field_stride + dst] = sbp[f * Sb.field_stride + src];
+        v[f] = src[f * sfs];
+#pragma unroll
+    for (int f = 0; f < NFIELD; ++f)
+        out[f * B.field_stride] = v[f];
 }
 
 // Per-block norms from per-tile partial sums, a workgroup per block: thread
