@@ -37,8 +37,9 @@ __device__ __forceinline__ double wave_sums(double (&v)[N], unsigned lane)
 // first derivatives.  What bounds it, as the stage kernel: latency.
 // Measured (96 blocks of 24^3 with matter): 0.812 ms with the whole halo box
 // in LDS, 400 registers and 8x8x8 tiles, 0.473 ms on 8x8x4 tiles, 0.327 ms
-// in this form at two waves per SIMD; three (168 registers, 53 spilled) take
-// 0.379 ms.
+// in this form at two waves per SIMD (three, 168 registers and 53 spilled,
+// 0.379 ms), 0.282 with the sums above, 0.269 without the points that only
+// the dissipation reads.
 template <int P, int TX, int TY, int TZ, int WPE, bool GEN>
 __global__ void __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 cons_kernel(const StageArgs a)
@@ -67,7 +68,7 @@ cons_kernel(const StageArgs a)
     const long long fs = B.field_stride;
     const Fac<R> F = table_entry((const Fac<R> *)a.fac64, T.block);
 
-    FieldTile<P, TX, TY, TZ, GEN> ft;
+    FieldTile<P, TX, TY, TZ, GEN, false> ft;   // no dissipation
     ft.setup(a, T, B, t, pl, zc, zs, ys);
     auto stage = [&](auto FC) __attribute__((always_inline)) {
         constexpr int FF = decltype(FC)::value;

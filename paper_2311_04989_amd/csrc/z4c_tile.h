@@ -277,7 +277,8 @@ __host__ __device__ constexpr bool mixed_field(int f)
 // GEN (frozen and neighbour rules): the array and block that the (x, y) part
 // refers to depend on whether the plane lies below, in or above the block,
 // so a thread keeps one pointer for each (`below`, `in`, `above`).
-template <int P, int TX, int TY, int TZ, bool GEN>
+// KO: with the outermost points, which only the dissipation reads.
+template <int P, int TX, int TY, int TZ, bool GEN, bool KO>
 struct ColStager {
     using D = ColDims<P, TX, TY, TZ>;
     double pf[D::LZ];
@@ -299,6 +300,8 @@ struct ColStager {
         ca = inx && iny;
         cb = cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
         cf = (inx || iny) && cy < D::LY;
+        if (!KO)   // one point less on every side
+            cf = cf && cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
         own = a.u + B.offset;
         fs = B.field_stride;
         // ragged tiles: points beyond the stored region are clamped into it
@@ -356,7 +359,7 @@ struct ColStager {
                     ld(D::LZ - 1 - q);
                 }
             }
-            if (ca) {
+            if (KO && ca) {
                 ld(0);
                 ld(D::LZ - 1);
             }
@@ -414,11 +417,11 @@ __device__ __forceinline__ void axis(const double *c, double c0, R f1, R f2, R f
 }
 
 // The staged field of a tile in LDS and this thread's view of it.
-template <int P, int TX, int TY, int TZ, bool GEN>
+template <int P, int TX, int TY, int TZ, bool GEN, bool KO = true>
 struct FieldTile {
     using D = ColDims<P, TX, TY, TZ>;
     using MZ = MixDimsZ<P, TX, TY, TZ>;
-    ColStager<P, TX, TY, TZ, GEN> st;
+    ColStager<P, TX, TY, TZ, GEN, KO> st;
     double *pl, *zc, *zs, *ys;      // plane part, interior columns, z and y sums
     // LDS offsets of this thread (opaque to the compiler, so that they are
     // kept and not formed again for each field): its column in pl, zc and zs;
@@ -475,7 +478,7 @@ struct FieldTile {
         }
         if (st.ca) {
 #pragma unroll
-            for (int q = 0; q < D::LZ; ++q)
+            for (int q = KO ? 0 : 1; q < D::LZ - (KO ? 0 : 1); ++q)
                 zc[q * TX * TY + zcol] = st.pf[q];
         }
         if constexpr (MIX) {
