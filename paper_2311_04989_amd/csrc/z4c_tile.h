@@ -288,8 +288,10 @@ struct ColStager {
     unsigned xy;                           // !GEN: byte offset of the column within a plane
     const double *below, *in, *above;      // GEN
     int qa;                                // GEN: first plane above the block (uniform)
-    // interior column; column the z sums read; column of the x or y stencils
-    bool ca, cb, cf;
+    // interior column; column of the x or y stencils; column whose z sums the
+    // mixed derivatives read (no corners: they are x or y stencils of them);
+    // column that the x and y sums of a mixed field read besides
+    bool ca, cf, cz, cm;
 
     __device__ __forceinline__ void setup(const StageArgs &a, const Tile &T, const z4c_block &B,
                                           unsigned t)
@@ -298,10 +300,10 @@ struct ColStager {
         const int sy = B.nx + 2 * ng, sz = sy * (B.ny + 2 * ng);
         const bool inx = cx >= D::RAD && cx < D::RAD + TX, iny = cy >= D::RAD && cy < D::RAD + TY;
         ca = inx && iny;
-        cb = cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
-        cf = (inx || iny) && cy < D::LY;
-        if (!KO)   // one point less on every side
-            cf = cf && cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
+        const bool cb = cx >= 1 && cx < D::LX - 1 && cy >= 1 && cy < D::LY - 1;
+        cz = cb && (inx || iny);
+        cf = KO ? (inx || iny) && cy < D::LY : cz;
+        cm = cb || cf;
         own = a.u + B.offset;
         fs = B.field_stride;
         // ragged tiles: points beyond the stored region are clamped into it
@@ -347,12 +349,12 @@ struct ColStager {
     __device__ __forceinline__ void prefetch(int f)
     {
         auto load = [&](auto ld) __attribute__((always_inline)) {
-            if (MIX ? (cb || cf) : cf) {
+            if (MIX ? cm : cf) {
 #pragma unroll
                 for (int q = D::RAD; q < D::RAD + TZ; ++q)
                     ld(q);
             }
-            if (MIX ? cb : ca) {
+            if (MIX ? cz : ca) {
 #pragma unroll
                 for (int q = 1; q < D::RAD; ++q) {
                     ld(q);
@@ -471,7 +473,7 @@ struct FieldTile {
             for (int q = 0; q < D::LZ; ++q)
                 st.pf[q] = double(float(st.pf[q]));
         }
-        if (MIX ? (st.cb || st.cf) : st.cf) {
+        if (MIX ? st.cm : st.cf) {
 #pragma unroll
             for (int z = 0; z < TZ; ++z)
                 pl[z * D::PLN + pcol] = st.pf[D::RAD + z];
@@ -482,7 +484,7 @@ struct FieldTile {
                 zc[q * TX * TY + zcol] = st.pf[q];
         }
         if constexpr (MIX) {
-            if (st.cb) {
+            if (st.cz) {
 #pragma unroll
                 for (int z = 0; z < TZ; ++z)
                     zs[z * MZ::ZR::PLANE + zrow] = d1raw<P, double, 1>(st.pf + z + D::RAD);
