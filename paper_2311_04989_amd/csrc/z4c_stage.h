@@ -43,10 +43,12 @@ __device__ __forceinline__ R lopc(const double *c, double c0, bool pos)
 // workgroups per CU, about equally HBM traffic.  Measured against the kernel
 // with the whole box in LDS and one workgroup per CU (256 points each
 // way): RK4 stage 2 of 512 blocks of 16^3 1.371 -> 1.004 ms (3.7 TB/s of HBM
-// traffic), RK4 step of 1,024 uneven blocks 18.3 -> 13.2 ms, of 8 x 128^3
-// blocks with matter 48.3 -> 28.9 ms (1.8 of it from the tile order).  3 % come from the wait for the
-// next field's points before a field's stores (1.036 and 13.5 ms without):
-// the stores then drain behind the next field instead of in front of it.
+// traffic), RK4 step of 1,024 uneven blocks 18.3 -> 13.1 ms, of 8 x 128^3
+// blocks with matter 48.3 -> 28.4 ms (1.8 of it from the tile order).  3 % come
+// from the wait for the next field's points before a field's stores (1.036 and
+// 13.5 ms without): the stores then drain behind the next field instead of in
+// front of it.  Requesting that field later, after the second barrier, takes
+// 1.022 ms.
 // Non-temporal stores are slower (1.15 ms): the 64-byte row pieces of x
 // neighbours no longer meet in L2.  With every load served from one block
 // (L2) the 512-block stage takes 0.63 ms.  A loop over tiles (work queue) in
