@@ -445,6 +445,13 @@ struct Master {
         const double nu = (1.0 + gam * eps) * iW;
         return mu * (nu + mu * rb) - 1.0;
     }
+    // Whether g(0) is -1 and not a NaN, as 0 D is from an infinite D (r^2, b^2 or
+    // q beyond double): such a cell has no sign change.
+    __device__ __forceinline__ bool starts() const
+    {
+        return r2 < INFINITY && b2 < INFINITY && rb2 < INFINITY
+            && !(gam * (q - 0.5 * b2) >= INFINITY);
+    }
     // g(mu) and the Newton step of f(mu) = mu - 1 / D, D = nu + mu rbar^2:
     // f / f' = D g / (D^2 + D').
     __device__ __forceinline__ double newton(double mu, double &step) const
@@ -611,8 +618,8 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
         // (h = 1), where g(mu+) = 0 up to rounding
         double W = 1.0, eps = 0.0, mu = M.mu_plus(), step;
         double lo = 0.0, flo = -1.0, hi = mu, fhi = M.newton(mu, step);
-        bool ok = fhi >= -1e-12;
-        if (fhi > 0.0) {
+        bool ok = fhi >= -1e-12 && M.starts();
+        if (ok && fhi > 0.0) {
             // Newton steps, held in the bracket by bisections: 2 to 5 on a
             // star; a step of 1e-9 leaves an error at rounding
             bool done = false;
