@@ -129,9 +129,10 @@ z4c_status z4c_sources_to_vc(const z4c_mplan *plan, int order, const double *adm
  *     function of Kastaun, Kalinani & Ciolfi (the algorithm the paper's
  *     primitive solver is based on): bracketed in [0, mu+] (mu+ from their
  *     auxiliary function), Newton steps held in the bracket until one is
- *     below max(tol, 1e-9) relative, and where that takes too long Illinois
- *     iterations to a relative width `tol`, each at most `max_iter`; no sign
- *     change or no convergence: atmosphere (status 3);
+ *     below max(tol, 1e-9) relative and its result has a residual below
+ *     max(tol, 1e-14); where that takes more than 16 steps or the residual is
+ *     larger, Illinois iterations to a relative width `tol`; each at most
+ *     `max_iter`; no sign change or no convergence: atmosphere (status 3);
  *   - a solution with |ut| = sqrt(W^2 - 1) above ut_max (the velocity
  *     ceiling), or with rho < f_thr rho_atm, becomes atmosphere (status 2 /
  *     status 1);
@@ -146,7 +147,7 @@ typedef struct {
     double rho_atm, p_atm; /* atmosphere density (> 0) and pressure (>= 0)             */
     double f_thr;          /* atmosphere threshold factor (>= 0; the paper uses 1)     */
     double ut_max;         /* velocity ceiling on |ut| (> 0; the paper uses 20)        */
-    double tol;            /* relative width of the final bracket of mu (> 0)          */
+    double tol;            /* relative tolerance of mu (> 0)                           */
     int max_iter;          /* >= 1                                                     */
 } z4c_c2p_params;
 

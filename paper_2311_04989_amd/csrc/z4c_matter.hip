@@ -287,7 +287,7 @@ struct C2PArgs {
     const z4c_mblock *blocks;
     const MTile *tiles;
     int ext, mhd, max_iter;
-    double gm1, chi_floor, rho_atm, p_atm, eps_atm, rho_thr, vmax2, ut_max2, tol, newton_tol;
+    double gm1, chi_floor, rho_atm, p_atm, eps_atm, rho_thr, vmax2, ut_max2, tol, newton_tol, g_tol;
     const double *geom;
     const double *prim_in;    // p2c
     double *cons;
@@ -420,9 +420,36 @@ __global__ void __launch_bounds__(PNT) p2c_kernel(const C2PArgs a)
 // d rbar^2 / d mu = -2 x^3 C, d qbar / d mu = -mu x^3 C, so that
 // s = qbar - mu rbar^2 + 1 has s' = mu x^3 C - rbar^2 and
 // nu' = s' (Gamma - (Gamma - 1) mu W) (mu W s' where eps is clamped).
+// What a root is worth is set by the rounding of one evaluation near it: errors
+// of mu^2 rbar^2 count W^2 times, those of qbar b^2 / D times (its terms cancel),
+// and those of the unit parts of s, 1 / W, D and mu as much as the rest where the
+// gas is slow and cold.  The products, x and b^2 r^2 - (r.b)^2 carry their
+// rounding errors along and the units are kept apart, some twenty fused operations;
+// one Newton result is then more exact than a bracket shrunk around a sign change
+// of the plain expressions (rms error of mu against 113-bit roots: W < 2 without
+// field 2.1e-16 -> 0.6e-16, W < 19 2.4e-16 -> 1.8e-16, b^2 / rho = 1 .. 10
+// 4.9e-16 -> 2.2e-16, 10^4 1.1e-12 -> 2.6e-16), where the plain expressions' Newton
+// result was less (6.2e-16 and 1.7e-12 with field).
 template <bool MHD>
 struct Master {
     double q, r2, b2, rb2, gam, vmax2;
+    double C, Cl, a0, a0l;   // b^2 r^2 - (r.b)^2 and q - b^2/2, value and remainder
+
+    __device__ __forceinline__ static double diff_error(double a, double b, double d)
+    {
+        const double bb = a - d;   // d = a - b rounded; the exact remainder
+        return (a - (d + bb)) + (bb - b);
+    }
+    __device__ __forceinline__ void prepare()
+    {
+        if constexpr (MHD) {
+            const double p = b2 * r2;
+            C = p - rb2;
+            Cl = diff_error(p, rb2, C) + fma(b2, r2, -p);
+            a0 = q - 0.5 * b2;
+            a0l = diff_error(q, 0.5 * b2, a0);
+        }
+    }
     __device__ __forceinline__ double x(double mu) const { return MHD ? 1.0 / (1.0 + mu * b2) : 1.0; }
     __device__ __forceinline__ double rbar2(double mu) const
     {
@@ -431,19 +458,49 @@ struct Master {
         const double xx = x(mu);
         return r2 * xx * xx + mu * xx * (1.0 + xx) * rb2;
     }
-    // g(mu); W and eps of the estimate
-    __device__ __forceinline__ double f(double mu, double &W, double &eps) const
+    // 1 / v to a few parts in 10^15: for a factor whose error is carried along or
+    // which scales a small correction
+    __device__ __forceinline__ static double inverse(double v)
     {
-        const double xx = x(mu);
-        const double rb = r2 * xx * xx + mu * xx * (1.0 + xx) * rb2;
-        const double qb = q - 0.5 * b2 - 0.5 * mu * mu * xx * xx * (b2 * r2 - rb2);
-        const double v2 = fmin(mu * mu * rb, vmax2);
-        const double iW = sqrt(1.0 - v2);
-        W = 1.0 / iW;
-        const double e = W * (qb - mu * rb + 1.0) - 1.0;
-        eps = e > 0.0 ? e : 0.0;
-        const double nu = (1.0 + gam * eps) * iW;
-        return mu * (nu + mu * rb) - 1.0;
+        const double i = __builtin_amdgcn_rcp(v);
+        return fma(fma(-v, i, 1.0), i, i);
+    }
+    // x, rbar^2, s = qbar - mu rbar^2 and t = 1 - mu^2 rbar^2 at mu
+    struct At {
+        double x, rb, s, t;
+    };
+    __device__ __forceinline__ At at(double mu) const
+    {
+        At e;
+        double qb = q, ql = 0.0;
+        if constexpr (MHD) {
+            const double p = mu * b2, d = 1.0 + p;
+            const double dl = (p > 1.0 ? (p - d) + 1.0 : (1.0 - d) + p) + fma(mu, b2, -p);
+            double x = inverse(d);
+            x = fma(fma(-d, x, 1.0), x, x);
+            e.x = x;
+            const double y = mu * x;
+            const double yl = (fma(-y, d, mu) - y * dl) * e.x;   // mu / (1 + mu b^2) - y
+            const double yy = y * y, yyl = fma(y, y, -yy) + 2.0 * y * yl;
+            const double T = C * yy, Tl = fma(C, yy, -T) + (C * yyl + Cl * yy);
+            qb = a0 - 0.5 * T;
+            ql = a0l - 0.5 * Tl;
+            ql = ql == ql ? ql : 0.0;   // a remainder of an infinity
+            e.rb = r2 * e.x * e.x + y * (1.0 + e.x) * rb2;
+        } else {
+            e.x = 1.0;
+            e.rb = r2;
+        }
+        e.s = fma(-mu, e.rb, qb) + ql;
+        const double p = mu * e.rb;
+        e.t = fma(-p, mu, 1.0) - fma(mu, e.rb, -p) * mu;
+        return e;
+    }
+    // D - 1, D = nu + mu rbar^2, from iw = 1 / W - 1: nu is 1 / W where eps is
+    // clamped, else Gamma (1 + s) - (Gamma - 1) / W.
+    __device__ __forceinline__ double d1(double mu, const At &p, double iw) const
+    {
+        return fma(mu, p.rb, p.s > iw ? fma(gam, p.s, -(gam - 1.0) * iw) : iw);
     }
     // Whether g(0) is -1 and not a NaN, as 0 D is from an infinite D (r^2, b^2 or
     // q beyond double): such a cell has no sign change.
@@ -452,30 +509,45 @@ struct Master {
         return r2 < INFINITY && b2 < INFINITY && rb2 < INFINITY
             && !(gam * (q - 0.5 * b2) >= INFINITY);
     }
-    // g(mu) and the Newton step of f(mu) = mu - 1 / D, D = nu + mu rbar^2:
-    // f / f' = D g / (D^2 + D').
-    __device__ __forceinline__ double newton(double mu, double &step) const
+    // g = mu D - 1; the unit parts of mu and D meet without a rounding
+    __device__ __forceinline__ static double residual(double mu, double D1)
     {
-        const double xx = x(mu), C = b2 * r2 - rb2;
-        const double rb = r2 * xx * xx + mu * xx * (1.0 + xx) * rb2;
-        const double mx3C = MHD ? mu * xx * xx * xx * C : 0.0;
-        const double qb = q - 0.5 * b2 - 0.5 * mu * mu * xx * xx * C;
-        const double v2r = mu * mu * rb;
-        const bool fast = v2r > vmax2;
-        const double t = 1.0 - (fast ? vmax2 : v2r);
-        const double W = rsqrt(t), iW = t * W;
-        const double e = W * (qb - mu * rb + 1.0) - 1.0;
-        const bool cold = !(e > 0.0);
-        const double nu = (1.0 + gam * (cold ? 0.0 : e)) * iW;
-        const double D = nu + mu * rb, g = mu * D - 1.0;
-        const double sp = mx3C - rb, mW = fast ? 0.0 : mu * W;
-        const double Dp = sp * (cold ? mW : gam - (fast ? 0.0 : gam - 1.0) * mW) + rb - 2.0 * mx3C;
+        const double m = mu - 1.0;
+        return fma(mu, D1, m) + (mu - (m + 1.0));
+    }
+    // g(mu); W and eps of the estimate
+    __device__ __forceinline__ double f(double mu, double &W, double &eps) const
+    {
+        const At p = at(mu);
+        const double t = fmax(p.t, 1.0 - vmax2), r = rsqrt(t), w = t * r;
+        const double iW = fma(0.5 * r, fma(-w, w, t), w), iw = iW - 1.0;
+        W = fma(r, fma(-iW, r, 1.0), r);
+        eps = p.s > iw ? W * (p.s - iw) : 0.0;
+        return residual(mu, d1(mu, p, iw));
+    }
+    // g(mu), the Newton step of f(mu) = mu - 1 / D, f / f' = D g / (D^2 + D'), and
+    // the iterate it leads to, from f without cancellation where the step is long
+    // (mu+ may be any factor above the root of a hot cell).
+    __device__ __forceinline__ double newton(double mu, double &step, double &next) const
+    {
+        const At p = at(mu);
+        const double mx3C = MHD ? mu * p.x * p.x * p.x * C : 0.0;
+        const bool fast = !(p.t >= 1.0 - vmax2);
+        const double t = fast ? 1.0 - vmax2 : p.t;
+        const double W = rsqrt(t), w = t * W, iw = fma(0.5 * W, fma(-w, w, t), w) - 1.0;
+        const double D1 = d1(mu, p, iw), D = 1.0 + D1, g = residual(mu, D1);
+        const double sp = mx3C - p.rb, mW = fast ? 0.0 : mu * W;
+        const double Dp = sp * (p.s > iw ? gam - (gam - 1.0) * mW : mW) + p.rb - 2.0 * mx3C;
         const double den = D * D + Dp;
         // the step needs few digits of its own: the iterate it leads to is
         // wrong by their error times the step
-        double inv = __builtin_amdgcn_rcp(den);
-        inv = fma(fma(-den, inv, 1.0), inv, inv);
-        step = D * g * inv;
+        step = D * g * inverse(den);
+        next = mu - step;
+        if (!(fabs(step) < 0.5 * mu)) {
+            const double r = Dp / D;
+            next = (1.0 + mu * r) / (D + r);
+            step = mu - next;
+        }
         return g;
     }
     // The root mu+ of mu sqrt(1 + rbar^2(mu)) - 1 (minimum enthalpy 1), by
@@ -486,15 +558,16 @@ struct Master {
     __device__ __forceinline__ double mu_plus() const
     {
         double hi = 1.0 / sqrt(1.0 + rbar2(1.0));
-        if constexpr (!MHD)
-            return hi;
+        if constexpr (!MHD) {   // the root itself: mu^2 (1 + r^2) = 1
+            const double p = hi * r2;
+            return fma(0.5 * hi, fma(-p, hi, 1.0) - fma(hi, hi, fma(hi, r2, -p) * hi), hi);
+        }
         double lo = 1.0 / sqrt(1.0 + r2), mu = hi;
-        const double C = b2 * r2 - rb2;
         for (int it = 0; it < 10 && hi - lo > 1e-15; ++it) {
             const double xx = x(mu);
             const double h = 1.0 + r2 * xx * xx + mu * xx * (1.0 + xx) * rb2;
             const double v = mu * mu * h - 1.0;
-            const double d = v / (2.0 * mu * (h - mu * xx * xx * xx * C));
+            const double d = v * inverse(2.0 * mu * (h - mu * xx * xx * xx * C));
             if (v > 0.0)
                 hi = mu;
             else
@@ -562,7 +635,7 @@ __device__ __forceinline__ bool illinois(Fn fn, double lo, double hi, double flo
 // iterations: Illinois steps for mu+ and for the root took 24 evaluations per
 // wave and bound the kernel by FP64 arithmetic (1.81 ms for 8.5 M cells of a
 // magnetised star and its atmosphere); Newton steps take 2 + 3, and it is
-// bound by HBM (0.377 ms, 4.2 of the 4.85 TB/s a large copy reaches).
+// bound by HBM (0.383 ms, 4.1 of the 4.85 TB/s a large copy reaches).
 template <bool MHD>
 __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
 {
@@ -614,23 +687,24 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
         M.rb2 = rb * rb;
         M.gam = a.gm1 + 1.0;
         M.vmax2 = a.vmax2;
+        M.prepare();
         // bracket [0, mu+] (g(0) = -1); mu+ is the root itself for cold gas
         // (h = 1), where g(mu+) = 0 up to rounding
-        double W = 1.0, eps = 0.0, mu = M.mu_plus(), step;
-        double lo = 0.0, flo = -1.0, hi = mu, fhi = M.newton(mu, step);
+        double W = 1.0, eps = 0.0, mu = M.mu_plus(), step, next;
+        double lo = 0.0, flo = -1.0, hi = mu, fhi = M.newton(mu, step, next);
         bool ok = fhi >= -1e-12 && M.starts();
         if (ok && fhi > 0.0) {
             // Newton steps, held in the bracket by bisections: 2 to 5 on a
-            // star; a step of 1e-9 leaves an error at rounding
+            // star; a step of 1e-9 leaves an error at rounding, and where it
+            // crossed the end of a clamp (of eps or v) g tells
             bool done = false;
             double g = fhi;
             for (int it = 0; it < a.max_iter && it < 16; ++it) {
-                const double m = mu - step;
-                done = fabs(step) <= a.newton_tol * mu && m > 0.0;
-                mu = done || (m > lo && m < hi) ? m : 0.5 * (lo + hi);
+                done = fabs(step) <= a.newton_tol * mu && next > 0.0;
+                mu = done || (next > lo && next < hi) ? next : 0.5 * (lo + hi);
                 if (done)
                     break;
-                g = M.newton(mu, step);
+                g = M.newton(mu, step, next);
                 if (g < 0.0) {
                     lo = mu;
                     flo = g;
@@ -639,16 +713,19 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
                     fhi = g;
                 }
             }
-            if (!done) {
+            g = M.f(mu, W, eps);
+            if (!done || fabs(g) > a.g_tol) {
                 double Wd, ed;
                 auto fm = [&](double m) { return M.f(m, Wd, ed); };
                 ok = illinois(fm, lo, hi, flo, fhi, a.tol, a.max_iter, mu);
+                M.f(mu, W, eps);
             }
+        } else {
+            M.f(mu, W, eps);
         }
         if (!ok) {
             st = 3;
         } else {
-            M.f(mu, W, eps);
             const double xx = M.x(mu);
             const double s = mu * xx;
             ut[0] = W * s * (ru[0] + mu * rb * bu[0]);
@@ -1046,6 +1123,7 @@ static z4c_status c2p_common(const z4c_mplan *P, const z4c_c2p_params *c, int ex
     A.vmax2 = A.ut_max2 / (1.0 + A.ut_max2);
     A.tol = c->tol;
     A.newton_tol = std::max(c->tol, 1e-9);
+    A.g_tol = std::max(c->tol, 1e-14);
     A.geom = (const double *)geom;
     return Z4C_OK;
 }
