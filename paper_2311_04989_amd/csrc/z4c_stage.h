@@ -6,32 +6,6 @@
 namespace z4c {
 namespace tile {
 
-// Lopsided first derivative along one axis, unscaled (same 1/(c1 h) factor
-// as the centred one): the order-P stencil on the points shifted by one
-// towards the side `pos` (offsets -P/2+1 .. P/2+1 when pos, mirrored
-// otherwise), in differences from the centre.  Weights, exact on
-// polynomials of degree <= P: order 6 (2, -24, -35, 80, -30, 8, -1) / 60 at
-// offsets -2 .. 4; order 4 (-3, -10, 18, -6, 1) / 12 at offsets -1 .. 3.
-template <int P, typename R, int ST>
-__device__ __forceinline__ R lopc(const double *c, double c0, bool pos)
-{
-    constexpr int RAD = P / 2 + 1;
-    double a[P / 2 + 2], b[P / 2 + 2];   // a: the shifted side, b: the other
-#pragma unroll
-    for (int q = 1; q <= RAD; ++q) {
-        const double pq = c[(RAD + q) * ST], mq = c[(RAD - q) * ST];
-        a[q] = pos ? pq : mq;
-        b[q] = pos ? mq : pq;
-    }
-    R v;
-    if constexpr (P == 4)
-        v = -R(3) * R(b[1] - c0) + R(18) * R(a[1] - c0) - R(6) * R(a[2] - c0) + R(a[3] - c0);
-    else
-        v = R(2) * R(b[2] - c0) - R(24) * R(b[1] - c0) + R(80) * R(a[1] - c0)
-            - R(30) * R(a[2] - c0) + R(8) * R(a[3] - c0) - R(a[4] - c0);
-    return pos ? v : -v;
-}
-
 // Fused right-hand side (+ Runge-Kutta stage) kernel.  Field order: shift,
 // conformal metric, Gamma-tilde, lapse, chi, Khat, Theta, At.  Each field's
 // right-hand side is finished as soon as its last contribution is known and,
@@ -59,8 +33,8 @@ __device__ __forceinline__ R lopc(const double *c, double c0, bool pos)
 // M_i, Theta and Z^i formed from the derivatives the stage takes anyway,
 // written to a.cons (when not null) and summed per tile into a.partial as
 // the constraint kernel does (same per-tile order).
-// LOP: lopsided stencils in the advection terms beta^k d_k u (re-read from
-// the staged field in LDS); every other derivative stays centred.
+// LOP: lopsided stencils in the advection terms beta^k d_k u; every other
+// derivative stays centred.
 // NAIVE (right-hand side, float arithmetic only): every staged value is
 // rounded to float before the stencil differences (the naive FP32 form).
 template <int P, int TX, int TY, int TZ, int WPE, typename R, int MODE, bool GEN, bool MON = false,
@@ -153,14 +127,6 @@ stage_kernel(const StageArgs a)
         };
         ft.st.template prefetch<mixed_field(BETAX)>(BETAX);
         auto staged = [&]() __attribute__((always_inline)) { return ft.centre(); };
-        auto derivs1 = [&](R d[3], R &ko) __attribute__((always_inline)) {
-            R xx, yy, zz;
-            ft.pure(F, d, xx, yy, zz, ko);
-        };
-        auto derivs2 = [&](R d[3], R dd[6], R &ko) __attribute__((always_inline)) {
-            ft.pure(F, d, dd[0], dd[3], dd[5], ko);
-            ft.mixed(F, dd);
-        };
         auto centre = [&](int f) __attribute__((always_inline)) {
             return active ? R(at(ub + f * fs, upt8)) : R(0);
         };
@@ -210,15 +176,27 @@ stage_kernel(const StageArgs a)
         const R alpha = active ? R(at(ub + ALPHA * fs, upt8)) : R(1);
         const R pi = R(PI);
 
+        // Derivatives of the staged field; LOP: the lopsided ones in lop.
+        R lop[3];
+        auto pure = [&](R d[3], R &xx, R &yy, R &zz, R &ko) __attribute__((always_inline)) {
+            if constexpr (LOP)
+                ft.pure_lopsided(F, beta, d, xx, yy, zz, ko, lop);
+            else
+                ft.pure(F, d, xx, yy, zz, ko);
+        };
+        auto derivs1 = [&](R d[3], R &ko) __attribute__((always_inline)) {
+            R xx, yy, zz;
+            pure(d, xx, yy, zz, ko);
+        };
+        auto derivs2 = [&](R d[3], R dd[6], R &ko) __attribute__((always_inline)) {
+            pure(d, dd[0], dd[3], dd[5], ko);
+            ft.mixed(F, dd);
+        };
         auto adv = [&](const R d[3]) __attribute__((always_inline)) {
-            if constexpr (LOP) {
-                const double c0 = staged();
-                return beta[0] * (lopc<P, R, 1>(ft.xtaps(), c0, beta[0] > R(0)) * F.d1[0])
-                     + beta[1] * (lopc<P, R, D::PX>(ft.ytaps(), c0, beta[1] > R(0)) * F.d1[1])
-                     + beta[2] * (lopc<P, R, TX * TY>(ft.ztaps(), c0, beta[2] > R(0)) * F.d1[2]);
-            } else {
+            if constexpr (LOP)
+                return beta[0] * lop[0] + beta[1] * lop[1] + beta[2] * lop[2];
+            else
                 return beta[0] * d[0] + beta[1] * d[1] + beta[2] * d[2];
-            }
         };
         // Monitor: constraint q at this point (0 where inactive) to a.cons,
         // and its |c|, c^2 summed over the wave (butterfly) into mred.

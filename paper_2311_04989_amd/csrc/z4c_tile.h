@@ -418,6 +418,32 @@ __device__ __forceinline__ void axis(const double *c, double c0, R f1, R f2, R f
     }
 }
 
+// Lopsided first derivative along one axis, unscaled (same 1/(c1 h) factor
+// as the centred one): the order-P stencil on the points shifted by one
+// towards the side `pos` (offsets -P/2+1 .. P/2+1 when pos, mirrored
+// otherwise), in differences from the centre.  Weights, exact on
+// polynomials of degree <= P: order 6 (2, -24, -35, 80, -30, 8, -1) / 60 at
+// offsets -2 .. 4; order 4 (-3, -10, 18, -6, 1) / 12 at offsets -1 .. 3.
+template <int P, typename R, int ST>
+__device__ __forceinline__ R lopc(const double *c, double c0, bool pos)
+{
+    constexpr int RAD = P / 2 + 1;
+    double a[P / 2 + 2], b[P / 2 + 2];   // a: the shifted side, b: the other
+#pragma unroll
+    for (int q = 1; q <= RAD; ++q) {
+        const double pq = c[(RAD + q) * ST], mq = c[(RAD - q) * ST];
+        a[q] = pos ? pq : mq;
+        b[q] = pos ? mq : pq;
+    }
+    R v;
+    if constexpr (P == 4)
+        v = -R(3) * R(b[1] - c0) + R(18) * R(a[1] - c0) - R(6) * R(a[2] - c0) + R(a[3] - c0);
+    else
+        v = R(2) * R(b[2] - c0) - R(24) * R(b[1] - c0) + R(80) * R(a[1] - c0)
+            - R(30) * R(a[2] - c0) + R(8) * R(a[3] - c0) - R(a[4] - c0);
+    return pos ? v : -v;
+}
+
 // The staged field of a tile in LDS and this thread's view of it.
 template <int P, int TX, int TY, int TZ, bool GEN, bool KO = true>
 struct FieldTile {
@@ -533,6 +559,28 @@ struct FieldTile {
         axis<P, R, 1>(xtaps(), c0, F.d1[0], F.d2[0], F.ko[0], d[0], xx, kx);
         axis<P, R, D::PX>(ytaps(), c0, F.d1[1], F.d2[1], F.ko[1], d[1], yy, ky);
         axis<P, R, TX * TY>(ztaps(), c0, F.d1[2], F.d2[2], F.ko[2], d[2], zz, kz);
+        ko = kx + ky + kz;
+    }
+    // The same with the lopsided first derivatives l for a shift `beta`, an axis
+    // finished before the taps of the next are read: with those of all three axes
+    // in flight the compiler spilled values that live through the whole kernel,
+    // and each reload waited behind the next field's points (ragged blocks of
+    // 20/13/33 x 19 points 494 us, so 424).
+    template <typename R>
+    __device__ __forceinline__ void pure_lopsided(const Fac<R> &F, const R beta[3], R d[3], R &xx,
+                                                  R &yy, R &zz, R &ko, R l[3]) const
+    {
+        const double c0 = centre();
+        R kx, ky, kz;
+        axis<P, R, 1>(xtaps(), c0, F.d1[0], F.d2[0], F.ko[0], d[0], xx, kx);
+        l[0] = lopc<P, R, 1>(xtaps(), c0, beta[0] > R(0)) * F.d1[0];
+        __builtin_amdgcn_sched_barrier(0);
+        axis<P, R, D::PX>(ytaps(), c0, F.d1[1], F.d2[1], F.ko[1], d[1], yy, ky);
+        l[1] = lopc<P, R, D::PX>(ytaps(), c0, beta[1] > R(0)) * F.d1[1];
+        __builtin_amdgcn_sched_barrier(0);
+        axis<P, R, TX * TY>(ztaps(), c0, F.d1[2], F.d2[2], F.ko[2], d[2], zz, kz);
+        l[2] = lopc<P, R, TX * TY>(ztaps(), c0, beta[2] > R(0)) * F.d1[2];
+        __builtin_amdgcn_sched_barrier(0);
         ko = kx + ky + kz;
     }
     // Mixed second derivatives, from the sums (formed in double also for
