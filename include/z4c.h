@@ -318,7 +318,8 @@ z4c_status z4c_step_graph(z4c_plan *plan, const z4c_step_desc *desc, int *result
  * the same key (device architecture, order, arithmetic, advection, halo
  * rule, block interior size, ghosts) take the stored launch without timing,
  * and the others are added to it.  Results are readable with
- * z4c_plan_get_launch.  Synchronises the stream. */
+ * z4c_plan_get_launch.  Synchronises the stream (one being captured is
+ * refused).  A call that fails leaves the plan and the cache as they were. */
 z4c_status z4c_plan_autotune(z4c_plan *plan, const double *u0, double *u0_out, double *u1,
                              const double *matter, int reps, void *stream);
 

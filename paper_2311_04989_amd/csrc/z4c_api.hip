@@ -194,7 +194,6 @@ struct z4c_plan {
     hipStream_t capture_stream = nullptr;
     std::vector<GraphEntry> graphs;
     int version = 0;
-    int num_cus = 256;
     // host copy of the neighbour table (nblocks*27) once set
     std::vector<int> nbr_h;
     // radiative outer boundary (z4c_plan_set_sommerfeld): block origins and
@@ -981,12 +980,7 @@ z4c_status z4c_plan_create(const z4c_params *params, const z4c_block *blocks, in
     P->total_ghost = gs[nblocks];
     P->total_pts = ps[nblocks];
     if (P->device) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess)
-            e = hipDeviceGetAttribute(&P->num_cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = hipMalloc(&P->blocks_d, sizeof(z4c_block) * nblocks);
+        hipError_t e = hipMalloc(&P->blocks_d, sizeof(z4c_block) * nblocks);
         if (e == hipSuccess)
             e = hipMemcpy(P->blocks_d, blocks, sizeof(z4c_block) * nblocks, hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -1486,6 +1480,35 @@ z4c_status z4c_step_graph(z4c_plan *P, const z4c_step_desc *d, int *result, void
     return Z4C_OK;
 }
 
+// Time of `reps` Runge-Kutta stages of the plan, after one to warm up.
+static z4c_status time_stage(z4c_plan *P, const double *u0, double *u0_out, double *u1,
+                             const double *matter, int reps, hipStream_t s, float *ms)
+{
+    const z4c_rk_coeffs c{0.0, 1.0 / 3.0, 0.0, 0.0, 1.0, 0.5, 1, 1};
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipError_t e = hipEventCreate(&e0);
+    if (e == hipSuccess)
+        e = hipEventCreate(&e1);
+    z4c_status st = Z4C_OK;
+    if (e == hipSuccess)
+        st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);
+    if (e == hipSuccess)
+        e = hipEventRecord(e0, s);
+    for (int r = 0; r < reps && e == hipSuccess && st == Z4C_OK; ++r)
+        st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &c, 1e-3, s);
+    if (e == hipSuccess)
+        e = hipEventRecord(e1, s);
+    if (e == hipSuccess)
+        e = hipEventSynchronize(e1);
+    if (e == hipSuccess)
+        e = hipEventElapsedTime(ms, e0, e1);
+    if (e0)
+        (void)hipEventDestroy(e0);
+    if (e1)
+        (void)hipEventDestroy(e1);
+    return st != Z4C_OK || e == hipSuccess ? st : hip_fail(e, "stage timing");
+}
+
 z4c_status z4c_plan_autotune(z4c_plan *P, const double *u0, double *u0_out, double *u1,
                              const double *matter, int reps, void *stream)
 {
@@ -1500,52 +1523,46 @@ z4c_status z4c_plan_autotune(z4c_plan *P, const double *u0, double *u0_out, doub
     z4c_status st = need_device(P);
     if (st != Z4C_OK)
         return st;
+    hipStream_t s = (hipStream_t)stream;
+    hipStreamCaptureStatus capture;
+    HIP_TRY(hipStreamIsCapturing(s, &capture), "hipStreamIsCapturing");
+    if (capture != hipStreamCaptureStatusNone)
+        return fail(Z4C_ENOTSUP, "autotune synchronises its stream, which is being captured");
     // One kernel serves every launch shape of a scheme, so there is one
     // candidate: its tiles, one workgroup each.  The recorded time is that of
-    // the dispatch the class is part of.
-    hipStream_t s = (hipStream_t)stream;
+    // the dispatch the class is part of.  The plan and the cache change only
+    // when everything has succeeded.
     const z4c_launch own{TILE_X, TILE_Y, TILE_Z, 0, 2};
     TuneCache cache = tune_cache_load();
-    bool fresh = false;
-    float ms = 0.f;
-    for (SizeClass &c : P->classes) {
+    std::vector<z4c_launch> pick;
+    std::vector<std::string> fresh;
+    for (const SizeClass &c : P->classes) {
         const std::string key = tune_key(P, c);
         const auto hit = cache.entries.find(key);
         if (hit != cache.entries.end()
             && stage_shape_supported(P->params.fd_order, hit->second.launch.tile_x,
                                      hit->second.launch.tile_y, hit->second.launch.tile_z,
                                      hit->second.launch.waves)) {
-            c.launch = hit->second.launch;
-            continue;
+            pick.push_back(hit->second.launch);
+        } else {
+            pick.push_back(own);
+            fresh.push_back(key);
         }
-        if (!fresh) {
-            const z4c_rk_coeffs co{0.0, 1.0 / 3.0, 0.0, 0.0, 1.0, 0.5, 1, 1};
-            hipEvent_t e0, e1;
-            HIP_TRY(hipEventCreate(&e0), "hipEventCreate");
-            if (const hipError_t e = hipEventCreate(&e1); e != hipSuccess) {
-                (void)hipEventDestroy(e0);
-                return hip_fail(e, "hipEventCreate");
-            }
-            st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &co, 1e-3, s);   // warm-up
-            (void)hipEventRecord(e0, s);
-            for (int r = 0; r < reps && st == Z4C_OK; ++r)
-                st = enqueue_stage(P, u0, u0_out, u1, u0, matter, &co, 1e-3, s);
-            (void)hipEventRecord(e1, s);
-            (void)hipEventSynchronize(e1);
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            (void)hipEventDestroy(e0);
-            (void)hipEventDestroy(e1);
-            if (st != Z4C_OK)
-                return st;
-        }
-        fresh = true;
-        c.launch = own;
-        cache.entries[key] = TuneEntry{own, ms / reps};
     }
-    count_tiles(P);
-    if (fresh)
-        tune_cache_store(cache);
+    if (!fresh.empty()) {
+        float ms = 0.f;
+        st = time_stage(P, u0, u0_out, u1, matter, reps, s, &ms);
+        if (st != Z4C_OK)
+            return st;
+        for (const std::string &key : fresh)
+            cache.entries[key] = TuneEntry{own, ms / reps};
+    }
     HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    for (size_t n = 0; n < pick.size(); ++n)
+        P->classes[n].launch = pick[n];
+    count_tiles(P);
+    if (!fresh.empty())
+        tune_cache_store(cache);
     return Z4C_OK;
 }
 
