@@ -818,8 +818,12 @@ hipError_t launch_interp(int order, const z4c_mplan *P, int ext, const double *i
     const int n = TO_CC ? P->n_cc : P->n_vc, fields = TO_CC ? 7 : 10;
     if (n == 0)
         return hipSuccess;
-    // a workgroup per column and field, where a grid can hold them
-    const int nf = n <= INT32_MAX / fields ? 1 : fields, grid = nf == 1 ? n * fields : n;
+    // a workgroup per column and field where a grid, which holds less than 2^32
+    // threads, can hold them, else as few fields in turn as it takes
+    int nf = 1;
+    while (nf < fields && (long long)n * ((fields + nf - 1) / nf) > UINT32_MAX / INT_)
+        ++nf;
+    const int grid = n * ((fields + nf - 1) / nf);
     if (order == 2)
         interp_kernel<2, TO_CC><<<grid, INT_, 0, s>>>(P->blocks_d, tiles, n, nf, ext, in, out);
     else if (order == 4)
