@@ -2,7 +2,9 @@
 // kernels (those live in z4c_tile.h, instantiated in z4c_variants_*.hip):
 // ghost refresh, per-block norm reduction, non-finite scan, and the dispatch
 // to the tile-kernel variants.
+#include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <type_traits>
 #include <utility>
 
@@ -107,27 +109,30 @@ __global__ void __launch_bounds__(256) ghost_kernel(const GhostArgs g, long long
 constexpr int NORM_THREADS = 1024, NORM_GROUPS = NORM_THREADS / 16;
 
 __global__ void __launch_bounds__(NORM_THREADS)
-norm_reduce_kernel(const z4c_block *blocks, const long long *tile_start, const int *tile_count,
-                   const double *partial, double *norms)
+norm_reduce_kernel(const z4c_block *blocks, int nblocks, const long long *tile_start,
+                   const int *tile_count, const double *partial, double *norms)
 {
     __shared__ double sum[NORM_THREADS];
-    const int b = blockIdx.x, t = threadIdx.x;
-    const double *p = partial + tile_start[b] * 16 + t % 16;
-    const int n = tile_count[b];
-    double s = 0.0;
+    const int t = threadIdx.x;
+    for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        const double *p = partial + tile_start[b] * 16 + t % 16;
+        const int n = tile_count[b];
+        double s = 0.0;
 #pragma unroll 4
-    for (int k = t / 16; k < n; k += NORM_GROUPS)
-        s += p[k * 16LL];
-    sum[t] = s;
-    __syncthreads();
-    for (int h = NORM_THREADS / 2; h >= 16; h >>= 1) {
-        if (t < h)
-            sum[t] += sum[t + h];
+        for (int k = t / 16; k < n; k += NORM_GROUPS)
+            s += p[k * 16LL];
+        sum[t] = s;
         __syncthreads();
-    }
-    if (t < 16) {
-        const z4c_block B = blocks[b];
-        norms[b * 16LL + t] = sum[t] * (B.dx * B.dy * B.dz);
+        for (int h = NORM_THREADS / 2; h >= 16; h >>= 1) {
+            if (t < h)
+                sum[t] += sum[t + h];
+            __syncthreads();
+        }
+        if (t < 16) {
+            const z4c_block B = blocks[b];
+            norms[b * 16LL + t] = sum[t] * (B.dx * B.dy * B.dz);
+        }
+        __syncthreads();   // before the next block's sums
     }
 }
 
@@ -206,8 +211,10 @@ hipError_t launch_norm_reduce(const z4c_block *blocks, int nblocks, const long l
                               const int *tile_count, const double *partial, double *norms,
                               hipStream_t s)
 {
-    norm_reduce_kernel<<<dim3(nblocks), dim3(NORM_THREADS), 0, s>>>(blocks, tile_start, tile_count,
-                                                                    partial, norms);
+    // a launch holds less than 2^32 threads; more blocks take turns
+    const unsigned grid = std::min((unsigned)nblocks, UINT32_MAX / NORM_THREADS);
+    norm_reduce_kernel<<<dim3(grid), dim3(NORM_THREADS), 0, s>>>(blocks, nblocks, tile_start,
+                                                                 tile_count, partial, norms);
     return hipGetLastError();
 }
 
