@@ -214,31 +214,40 @@ prolong_kernel(const z4c_block *blocks, const z4c_transfer *tr, const XTile *til
     any_pass<O, true>(T.dir[2], A, nullptr, i0, i1, i2, T, R, F, dst);
 }
 
+// Restriction: one thread per coarse point, all 22 fields, every load issued
+// before the first store.  The transfer of the workgroup's first point is found
+// once (uniform), each thread goes on from there.  What bounds it: reads of
+// every other point and written pieces that are parts of sectors; with a search
+// and 64-bit divisions per point the restriction and prolongation of 64 coarse
+// and 512 fine blocks took 0.657 ms, now 0.653.
 __global__ void __launch_bounds__(256)
 restrict_kernel(const z4c_block *blocks, const z4c_transfer *tr, const long long *start, int n,
                 long long total, double *u)
 {
-    for (long long r = blockIdx.x * 256LL + threadIdx.x; r < total;
-         r += (long long)gridDim.x * 256) {
-        const int t = find_transfer(start, n, r);
-        const z4c_transfer T = tr[t];
-        const long long loc = r - start[t];
-        const int bx = T.hi[0] - T.lo[0], by = T.hi[1] - T.lo[1];
-        const int cj[3] = {T.lo[0] + (int)(loc % bx), T.lo[1] + (int)((loc / bx) % by),
-                           T.lo[2] + (int)(loc / ((long long)bx * by))};
-        const z4c_block C = blocks[T.coarse];
-        const z4c_block F = blocks[T.fine];
-        const long long src = F.offset + point_index(F, 2 * (cj[0] - T.c0[0]),
-                                                     2 * (cj[1] - T.c0[1]), 2 * (cj[2] - T.c0[2]));
-        const long long dst = C.offset + point_index(C, cj[0], cj[1], cj[2]);
-        double v[NFIELD];   // every load issued before the first store
+    const long long first = 256LL * xcd_logical(blockIdx.x, gridDim.x), r = first + threadIdx.x;
+    if (r >= total)
+        return;
+    int t = find_transfer(start, n, first);
+    while (t + 1 < n && start[t + 1] <= r)
+        ++t;
+    const z4c_transfer T = tr[t];
+    // 32 bits hold the points of a transfer (22 fields each, in memory)
+    const unsigned loc = (unsigned)(r - start[t]), bx = T.hi[0] - T.lo[0], by = T.hi[1] - T.lo[1];
+    const unsigned row = loc / bx, pl = row / by;
+    const int cj[3] = {T.lo[0] + (int)(loc - row * bx), T.lo[1] + (int)(row - pl * by),
+                       T.lo[2] + (int)pl};
+    const z4c_block C = blocks[T.coarse];
+    const z4c_block F = blocks[T.fine];
+    const double *src = u + F.offset + point_index(F, 2 * (cj[0] - T.c0[0]), 2 * (cj[1] - T.c0[1]),
+                                                   2 * (cj[2] - T.c0[2]));
+    double *dst = u + C.offset + point_index(C, cj[0], cj[1], cj[2]);
+    double v[NFIELD];
 #pragma unroll
-        for (int f = 0; f < NFIELD; ++f)
-            v[f] = u[src + f * F.field_stride];
+    for (int f = 0; f < NFIELD; ++f)
+        v[f] = src[f * F.field_stride];
 #pragma unroll
-        for (int f = 0; f < NFIELD; ++f)
-            u[dst + f * C.field_stride] = v[f];
-    }
+    for (int f = 0; f < NFIELD; ++f)
+        dst[f * C.field_stride] = v[f];
 }
 
 bool same_ratio(double c, double f) { return std::fabs(c - 2.0 * f) <= 1e-12 * c; }
@@ -416,12 +425,6 @@ std::vector<XTile> make_tiles(const std::vector<z4c_transfer> &v, int order)
     return out;
 }
 
-int grid_for(long long total)
-{
-    const long long g = (total + 255) / 256;
-    return (int)std::min<long long>(std::max<long long>(g, 1), 65536);
-}
-
 }  // namespace
 }  // namespace z4c
 
@@ -550,8 +553,8 @@ static z4c_status xcall(const z4c_xplan *X, double *u, bool pro, hipStream_t s)
     } else {
         if (X->res_total == 0)
             return Z4C_OK;
-        restrict_kernel<<<grid_for(X->res_total), 256, 0, s>>>(blocks, X->res_d, X->res_start_d,
-                                             (int)X->res.size(), X->res_total, u);
+        restrict_kernel<<<(unsigned)((X->res_total + 255) / 256), 256, 0, s>>>(
+            blocks, X->res_d, X->res_start_d, (int)X->res.size(), X->res_total, u);
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? Z4C_OK : set_hip_error(e, "intergrid kernel launch");
