@@ -130,7 +130,8 @@ __global__ void __launch_bounds__(RAD_THREADS) radiative_kernel(const RadiativeA
     if (gid >= a.total)
         return;
     // region of the workgroup's first point by binary search over the prefix
-    // sums, then of this thread's
+    // sums, then of this thread's (a region has at least ng points: the walk is
+    // a few steps)
     int lo = 0, hi = a.nregions;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;

@@ -9,8 +9,8 @@
 // LDS and applies the three direction rules one after the other (x, then
 // y, then z; an even fine index copies, an odd one takes `order` taps), the
 // z pass writing the fine points to HBM.  Restriction: one thread per
-// (destination point, field), the transfer found by a binary search over the
-// prefix sums of the box sizes.
+// destination point, which takes all fields, the transfer found by a binary
+// search over the prefix sums of the box sizes.
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
@@ -216,10 +216,13 @@ prolong_kernel(const z4c_block *blocks, const z4c_transfer *tr, const XTile *til
 
 // Restriction: one thread per coarse point, all 22 fields, every load issued
 // before the first store.  The transfer of the workgroup's first point is found
-// once (uniform), each thread goes on from there.  What bounds it: reads of
-// every other point and written pieces that are parts of sectors; with a search
-// and 64-bit divisions per point the restriction and prolongation of 64 coarse
-// and 512 fine blocks took 0.657 ms, now 0.653.
+// once (uniform), each thread walks on from there.  What bounds it: reads of
+// every other point and written pieces that are parts of sectors.  Against a
+// search and 64-bit divisions per point, 262,144 points: transfers of 512 points
+// 47.9 -> 46.9 us, of 64 points 51.8 -> 49.8, of 8 points (a walk of up to 31)
+// 49.8 -> 47.5; only at one point per transfer, 255 steps, it loses, 52.0 -> 54.9.
+// Doubled steps or a search up to the workgroup's last transfer gained nothing
+// (57.5 us at 64 points; 50.7 at 8).
 __global__ void __launch_bounds__(256)
 restrict_kernel(const z4c_block *blocks, const z4c_transfer *tr, const long long *start, int n,
                 long long total, double *u)
