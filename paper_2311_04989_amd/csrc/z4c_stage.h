@@ -59,11 +59,13 @@ stage_kernel(const StageArgs a)
     // At sources (chi to At stage); as many of the 27 as the LDS that the
     // staging leaves at this occupancy holds, the rest in registers.
     constexpr int WG_PER_CU = (4 * WPE * 64) / NT;
-    constexpr int SLOT_BUDGET =
-        (LDS_PER_CU / WG_PER_CU - 64 - (D::NPL + D::NZC + MZ::NZS + MZ::NYS) * (int)sizeof(double)
-         - (MON ? (NT / 64) * 16 * (int)sizeof(double) : 8))
-        / (NT * (int)sizeof(R));
+    constexpr int SHARE = LDS_PER_CU / LDS_GRANULE / WG_PER_CU * LDS_GRANULE;
+    constexpr int STAGED = (D::NPL + D::NZC + MZ::NZS + MZ::NYS) * (int)sizeof(double)
+                         + (MON ? (NT / 64) * 16 * (int)sizeof(double) : 8);
+    constexpr int SLOT_BUDGET = (SHARE - 64 - STAGED) / (NT * (int)sizeof(R));
     constexpr int NSLOT = SLOT_BUDGET < 27 ? SLOT_BUDGET : 27;
+    constexpr int GRANULES = (STAGED + NSLOT * NT * (int)sizeof(R) + LDS_GRANULE - 1) / LDS_GRANULE;
+    static_assert(GRANULES * WG_PER_CU * LDS_GRANULE <= LDS_PER_CU, "WG_PER_CU workgroups fit");
     static_assert(NSLOT > 0, "");
     __shared__ R slots[NSLOT * NT];
 

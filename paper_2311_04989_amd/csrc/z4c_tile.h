@@ -34,6 +34,7 @@ namespace tile {
 
 constexpr double PI = 3.14159265358979323846;
 constexpr int LDS_PER_CU = 163840;   // gfx950
+constexpr int LDS_GRANULE = 1280;    // a workgroup's LDS is allocated in these
 
 // Symmetric 3x3 index: xx 0, xy 1, xz 2, yy 3, yz 4, zz 5.
 __host__ __device__ constexpr int S(int i, int j)
