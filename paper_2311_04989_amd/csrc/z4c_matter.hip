@@ -423,13 +423,13 @@ __global__ void __launch_bounds__(PNT) p2c_kernel(const C2PArgs a)
 // What a root is worth is set by the rounding of one evaluation near it: errors
 // of mu^2 rbar^2 count W^2 times, those of qbar b^2 / D times (its terms cancel),
 // and those of the unit parts of s, 1 / W, D and mu as much as the rest where the
-// gas is slow and cold.  The products, x and b^2 r^2 - (r.b)^2 carry their
-// rounding errors along and the units are kept apart, some twenty fused operations;
+// gas is slow and cold.  The products, mu x and b^2 r^2 - (r.b)^2 carry their
+// rounding errors along and the units are kept apart, some dozen fused operations;
 // one Newton result is then more exact than a bracket shrunk around a sign change
 // of the plain expressions (rms error of mu against 113-bit roots: W < 2 without
 // field 2.1e-16 -> 0.6e-16, W < 19 2.4e-16 -> 1.8e-16, b^2 / rho = 1 .. 10
-// 4.9e-16 -> 2.2e-16, 10^4 1.1e-12 -> 2.6e-16), where the plain expressions' Newton
-// result was less (6.2e-16 and 1.7e-12 with field).
+// 4.9e-16 -> 2.2e-16, 10^4 1.1e-12 -> 3.1e-16), where the plain expressions' Newton
+// result was less with a field (6.2e-16 and 1.7e-12).
 template <bool MHD>
 struct Master {
     double q, r2, b2, rb2, gam, vmax2;
@@ -448,6 +448,10 @@ struct Master {
             Cl = diff_error(p, rb2, C) + fma(b2, r2, -p);
             a0 = q - 0.5 * b2;
             a0l = diff_error(q, 0.5 * b2, a0);
+            if (!(C < INFINITY)) {   // b^2 r^2 beyond double: qbar is -infinity
+                a0 = -C;
+                C = Cl = a0l = 0.0;
+            }
         }
     }
     __device__ __forceinline__ double x(double mu) const { return MHD ? 1.0 / (1.0 + mu * b2) : 1.0; }
@@ -474,18 +478,15 @@ struct Master {
         At e;
         double qb = q, ql = 0.0;
         if constexpr (MHD) {
-            const double p = mu * b2, d = 1.0 + p;
-            const double dl = (p > 1.0 ? (p - d) + 1.0 : (1.0 - d) + p) + fma(mu, b2, -p);
+            const double d = fma(mu, b2, 1.0), dl = fma(mu, b2, 1.0 - d);   // 1 - d is exact
             double x = inverse(d);
             x = fma(fma(-d, x, 1.0), x, x);
             e.x = x;
             const double y = mu * x;
-            const double yl = (fma(-y, d, mu) - y * dl) * e.x;   // mu / (1 + mu b^2) - y
-            const double yy = y * y, yyl = fma(y, y, -yy) + 2.0 * y * yl;
-            const double T = C * yy, Tl = fma(C, yy, -T) + (C * yyl + Cl * yy);
-            qb = a0 - 0.5 * T;
-            ql = a0l - 0.5 * Tl;
-            ql = ql == ql ? ql : 0.0;   // a remainder of an infinity
+            const double yl = fma(-y, dl, fma(-y, d, mu)) * x;   // mu / (1 + mu b^2) - y
+            const double Cy = C * y, Cyl = fma(Cl, y, fma(C, y, -Cy));
+            qb = fma(-0.5 * Cy, y, a0);
+            ql = fma(-Cy, yl, fma(-0.5 * y, Cyl, a0l));
             e.rb = r2 * e.x * e.x + y * (1.0 + e.x) * rb2;
         } else {
             e.x = 1.0;
@@ -692,19 +693,17 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
         // (h = 1), where g(mu+) = 0 up to rounding
         double W = 1.0, eps = 0.0, mu = M.mu_plus(), step, next;
         double lo = 0.0, flo = -1.0, hi = mu, fhi = M.newton(mu, step, next);
-        bool ok = fhi >= -1e-12 && M.starts();
+        bool ok = fhi >= -1e-12 && M.starts(), done = false;
         if (ok && fhi > 0.0) {
             // Newton steps, held in the bracket by bisections: 2 to 5 on a
             // star; a step of 1e-9 leaves an error at rounding, and where it
             // crossed the end of a clamp (of eps or v) g tells
-            bool done = false;
-            double g = fhi;
             for (int it = 0; it < a.max_iter && it < 16; ++it) {
                 done = fabs(step) <= a.newton_tol * mu && next > 0.0;
                 mu = done || (next > lo && next < hi) ? next : 0.5 * (lo + hi);
                 if (done)
                     break;
-                g = M.newton(mu, step, next);
+                const double g = M.newton(mu, step, next);
                 if (g < 0.0) {
                     lo = mu;
                     flo = g;
@@ -713,15 +712,14 @@ __global__ void __launch_bounds__(PNT) c2p_kernel(const C2PArgs a)
                     fhi = g;
                 }
             }
-            g = M.f(mu, W, eps);
-            if (!done || fabs(g) > a.g_tol) {
-                double Wd, ed;
-                auto fm = [&](double m) { return M.f(m, Wd, ed); };
-                ok = illinois(fm, lo, hi, flo, fhi, a.tol, a.max_iter, mu);
-                M.f(mu, W, eps);
-            }
-        } else {
-            M.f(mu, W, eps);
+        }
+        for (bool bracket = ok && fhi > 0.0;; bracket = false) {
+            const double g = M.f(mu, W, eps);
+            if (!bracket || (done && fabs(g) <= a.g_tol))
+                break;
+            double Wd, ed;
+            auto fm = [&](double m) { return M.f(m, Wd, ed); };
+            ok = illinois(fm, lo, hi, flo, fhi, a.tol, a.max_iter, mu);
         }
         if (!ok) {
             st = 3;
