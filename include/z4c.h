@@ -25,7 +25,7 @@
  *     for state field f (moffset / coffset for matter / constraints).
  *     Any offset works; interior rows that start on 64 bytes (offset + ng and
  *     the row and field strides multiples of 8) are written fastest: RK4 stage
- *     of 512 blocks of 16^3 + 4 ghosts 0.93 ms packed, 0.81 ms so.
+ *     of 512 blocks of 16^3 + 4 ghosts with u2 = u0 0.93 ms packed, 0.81 ms so.
  *   - Interior points are i in [0, nx) etc.; only interior points of an
  *     output array are written by the stage, RHS and constraint calls.
  *
@@ -159,9 +159,8 @@ z4c_status z4c_plan_set_params(z4c_plan *plan, const z4c_params *params);
 /* Same-level neighbour table (HOST, nblocks*27 ints, -1 = outer boundary),
  * entry [b*27 + (oz+1)*9 + (oy+1)*3 + (ox+1)] = block adjacent to b in
  * direction (ox, oy, oz).  Neighbours must have equal nx, ny, nz, ng and
- * field_stride.  Halo reads through the neighbour rule address a point of
- * another block by its 32-bit element offset from the state array base, so
- * they need offset + (nx+2ng)(ny+2ng)(nz+2ng) <= 2^32 for every block named
+ * field_stride.  Halo reads through the neighbour rule
+ * need offset + (nx+2ng)(ny+2ng)(nz+2ng) <= 2^32 for every block named
  * as another block's neighbour (34 GB of FP64 before its end); a table that
  * breaks this is accepted (ghost refreshes address in 64 bits) unless the
  * plan reads halos through the neighbour rule (Z4C_ENOTSUP, plan unchanged).

@@ -180,8 +180,9 @@ struct z4c_plan {
     bool has_nbr = false;
     bool periodic_ok = true;   // every block has nx, ny, nz >= ng
     // every block the neighbour table names for another block ends within
-    // 2^32 elements of the array base (halo reads address such points with
-    // 32-bit element offsets from the base)
+    // 2^32 elements of the array base: the stated limit of halo reads through the
+    // neighbour rule (the present kernels form 64-bit addresses and would reach
+    // further)
     bool nbr32 = true;
     int halo = Z4C_GHOST_NONE; // halo reads of z4c_rhs / z4c_rk_stage / z4c_constraints
     // level-jump exchange of Z4C_STEP_LEVEL_EXCHANGE: one transfer plan per

@@ -116,8 +116,9 @@ __device__ __forceinline__ void radiative_fields(const RadiativeArgs &a, long lo
 
 // One thread per outer point and part: it finds its samples once and takes the
 // fields in turn, the reads of the next RAD_AHEAD in flight.
-// What bounds it: memory latency (169,000 points of 8 x 40^3 are 5 waves per
-// SIMD) and the partial sectors of its pieces of 4 points.  Against a workgroup
+// What bounds it: memory latency (169,000 points of 8 x 40^3 would be 5 waves per
+// SIMD; the 168 registers of the stage mode, twelve held results and two fields in
+// flight, leave 3) and the partial sectors of its pieces of 4 points.  Against a workgroup
 // of a thread per (field, point), 32 points at a time, whose first 32 threads
 // found the samples and enforced while the others waited: 113 -> 78 us per stage
 // of 8 x 40^3, 42 -> 15 of 8 x 24^3; with all 22 fields in one thread 81 and 19.

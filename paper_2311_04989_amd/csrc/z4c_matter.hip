@@ -4,13 +4,13 @@
 // the perfect-fluid / ideal-GRMHD stress-energy tensor (Sec. 2.1, 2.2).
 //
 // Interpolation is separable and marches along z: a workgroup of 256
-// threads owns an ITX x ITY column of outputs and ITZ output planes; for each
-// input plane it stages the (ITX + order - 1)(ITY + order - 1) inputs in LDS
-// (the next planes already in flight in registers), reduces them along x and
-// then y, and each
-// thread keeps the y-reduced values of the last `order` planes in registers
-// for the z reduction, so every input plane is read once per column and the
-// z halo costs (order - 1) / ITZ extra planes.  The ADM projections are
+// threads owns a column of w x h outputs and d output planes of one field (even
+// shares of a block, chosen when the plan is made); for each input plane it stages
+// the (w + order - 1)(h + order - 1) inputs in LDS (the next planes already in
+// flight in registers), reduces them along x and then y, and each thread keeps
+// the y-reduced values of the last `order` planes in registers for the z
+// reduction, so every input plane is read once per column and the z halo costs
+// order - 1 planes in d.  The ADM projections are
 // pointwise, one cell per thread over contiguous chunks of stored cells.
 // Both kernels are HBM-bound.
 #include <algorithm>
@@ -778,8 +778,9 @@ void column_shape(int nx, int ny, int row, int &w, int &h)
     long long best = INT64_MAX;
     w = h = 1;
     for (int a = std::min(nx, 64); a >= 1; --a) {
-        // a thread per output, two per point of an input plane (rows of even
-        // length) and one per pair of x sums, at order 6; offsets below OUTSIDE
+        // at order 6: a thread per output, a thread per two points of an input
+        // plane (rows of even length), a thread per pair of x sums; offsets below
+        // OUTSIDE
         const int b = std::min({ny, INT_ / a, 2 * INT_ / ((a + 6) & ~1) - 5,
                                 INT_ / ((a + 1) / 2) - 5,
                                 std::max(1, (int)((OUTSIDE / 8 - 64) / row))});

@@ -3,8 +3,9 @@
 #pragma once
 // Tile kernels (one workgroup = one tile of TX*TY*TZ interior points of a
 // MeshBlock, one point per thread).  The state fields are staged one at a
-// time into LDS from a (TX+2R)(TY+2R)(TZ+2R) halo box, R = p/2 + 1 (the
-// Kreiss-Oliger half width); while a field is being differentiated the next
+// time from a (TX+2R)(TY+2R)(TZ+2R) halo box, R = p/2 + 1 (the Kreiss-Oliger
+// half width), into registers, a z-column per thread, and what the stencils of
+// others read of it into LDS; while a field is being differentiated the next
 // field's points are already in flight from HBM into registers.  Each
 // field's derivatives are consumed at once in a fixed order (stage kernel:
 // shift -> conformal metric -> Gamma-tilde -> lapse -> chi -> Khat, Theta ->
@@ -88,6 +89,10 @@ __device__ __forceinline__ R d1sum(const R *c)
 // Two-pass mixed derivatives of the stage kernel, z-pass first: zs = D_z u
 // over the tile extended by Q in x and y, ys = D_y u over the tile extended
 // by Q in x (unscaled sums); then xz = D_x(zs), yz = D_y(zs), xy = D_x(ys).
+// Six sums are read per derivative where the tensor product of differences reads
+// 36 values, at one rounding of the first derivative per point: off-diagonal
+// right-hand sides of At on the 64^3 star have an rms error of 2.7e-15 of their
+// size, by the tensor product 0.9e-15.
 // A z plane of NR rows of at most 16 sums: even rows 16 apart from the
 // plane's start, odd rows 16 apart from an offset of 8 mod 16, so that for
 // double sums any run of two to four consecutive rows, each read at 8
@@ -252,9 +257,11 @@ __device__ __forceinline__ T table_entry(const T *p, long long n)
 // registers.  That is 18 KB per field and tile instead of the whole box's
 // 37 KB, and a field without second derivatives loads 1,280 points instead
 // of 3,072.  With the sums and 25 values per thread parked in LDS, a
-// workgroup takes half a CU's LDS and its lanes half a SIMD's registers
-// without scratch: two workgroups per CU, whose barriers and memory waits
-// cover one another.
+// workgroup takes half a CU's LDS and its lanes half a SIMD's registers: two
+// workgroups per CU, whose barriers and memory waits cover one another.  That is
+// without scratch but for order 6 in double: the monitor form spills 16 registers
+// (22 with neighbour or frozen halos), the lopsided one 25 to 41, the plain one
+// none (2).
 template <int P, int TX, int TY, int TZ>
 struct ColDims {
     static constexpr int RAD = P / 2 + 1, Q = P / 2, NT = TX * TY * TZ;
