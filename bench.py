@@ -52,8 +52,8 @@ STAGE_BYTES = [3 * 176, 5 * 176, 5 * 176, 3 * 176]
 PROFILED_STAGE2 = {
     "tiles": {8: ((8, 8, 4), 0, 2), 16: ((8, 8, 4), 0, 2), 24: ((8, 8, 4), 0, 2),
               32: ((8, 8, 4), 0, 2)},
-    "fetch_kib": 4200000.0, "fetch_scale": 2.0,
-    "write_kib": 2726000.0, "write_scale": 1.0,
+    "fetch_kib": 4218000.0, "fetch_scale": 2.0,
+    "write_kib": 2742000.0, "write_scale": 1.0,
 }
 
 
